@@ -1253,7 +1253,8 @@ vl_status vl_model_autotune(vl_model* m, const float* pix, const int32_t* hs, co
                              o.op, cfg, o.e, s)
                    : gemm_bf16(o.A, o.lda, o.B, o.K, o.b8, T, o.N, o.K, o.op, cfg, o.e, s);
       };
-      for (int cfg = omx ? N_BF16_CFGS : 0; cfg < (omx ? N_GEMM_CFGS : N_BF16_CFGS); ++cfg) {
+      for (int cfg = 0; cfg < N_GEMM_CFGS; ++cfg) {
+        if (gemm_cfg_is_mx(cfg) != omx) continue;
         hipError_t err = launch(cfg);
         if (err != hipSuccess) continue;
         VL_HIP(hipEventRecord(e0, s));

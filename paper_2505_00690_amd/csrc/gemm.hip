@@ -16,6 +16,8 @@
 // FP32 path: LDS-tiled FMA kernel (64 x 64 tile, 4 x 4 per thread), the plain
 // FP32 baseline; and a few-rows FP32 kernel for the heads' small products
 // (pooled rows or embeddings against the projection or the texts).
+#include <algorithm>
+
 #include "gemm_kernels.hpp"
 
 namespace vl {
@@ -40,6 +42,15 @@ hipError_t gemm_launch_cfg7(const bf16_t*, int, const void*, int, bool, int, int
 hipError_t gemm_launch_cfg8(const bf16_t*, int, const void*, int, bool, int, int, int, int,
                                const EpiArgs&, hipStream_t);
 
+hipError_t gemm_launch_cfg13(const bf16_t*, int, const void*, int, bool, int, int, int, int,
+                                const EpiArgs&, hipStream_t);
+hipError_t gemm_launch_cfg14(const bf16_t*, int, const void*, int, bool, int, int, int, int,
+                                const EpiArgs&, hipStream_t);
+hipError_t gemm_launch_cfg15(const bf16_t*, int, const void*, int, bool, int, int, int, int,
+                                const EpiArgs&, hipStream_t);
+hipError_t gemm_launch_cfg16(const bf16_t*, int, const void*, int, bool, int, int, int, int,
+                                const EpiArgs&, hipStream_t);
+
 // ------------------------------------------------ MXFP8 GEMM configurations
 hipError_t gemm_mx_launch_cfg9(const uint8_t*, const uint8_t*, const uint8_t*, const uint8_t*,
                                int, int, int, int, const EpiArgs&, hipStream_t);
@@ -52,37 +63,51 @@ hipError_t gemm_mx_launch_cfg12(const uint8_t*, const uint8_t*, const uint8_t*, 
 
 const char* gemm_cfg_name(int cfg) {
   static const char* names[N_GEMM_CFGS] = {"DL_256x256_W2x4", "DL_256x256_W4x2", "DL_256x256_W2x2", "DL_128x128_W2x2", "DL_256x128_W2x2", "DL_128x256_W2x2", "REG_128x128_W2x2", "DL_192x256_W2x4",
-                                           "DL3_160x256_W1x8", "MX_160x256_W1x8", "MX_192x256_W2x4", "MX_128x256_W2x4", "MX_128x128_W2x2"};
+                                           "DL3_160x256_W1x8", "MX_160x256_W1x8", "MX_192x256_W2x4", "MX_128x256_W2x4", "MX_128x128_W2x2",
+                                           "S4_64x32_W2x1", "S4_64x64_W2x2", "S3_64x128_W2x4", "S4_128x128_W2x4"};
   return cfg >= 0 && cfg < N_GEMM_CFGS ? names[cfg] : "unknown";
 }
 
+// Estimated time of a tile configuration, from what one workgroup costs: a
+// launch takes base + (K / 64) max(lat, thr n) + epi n microseconds, n the
+// workgroups per CU, rounded up.  lat is a K tile's time when a CU has one
+// workgroup, thr its share of a full CU, epi a tile's prologue and epilogue.
+struct GemmCost {
+  int cfg, bm, bn;
+  double base, lat, thr, epi;
+};
+static double gemm_cost(const GemmCost& c, int M, int N, int K) {
+  const long tiles = (long)((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn);
+  const double n = (double)((tiles + 255) / 256);
+  return c.base + K / 64 * std::max(c.lat, c.thr * n) + c.epi * n;
+}
+
 int gemm_cfg_heuristic(int M, int N, int K, bool b_fp8) {
-  (void)K;
   (void)b_fp8;
-  // Estimated time in units of one 256 x 256 tile on one CU: rounds of tiles
-  // over the 256 CUs times the relative tile time (area / relative
-  // efficiency, from measurements on gfx950).  Small grids fall back to
-  // 128 x 128 tiles.
-  struct C { int cfg, bm, bn; double eff; };
-  static const C cands[] = {{CFG_DL_256x256_W2x4, 256, 256, 1.0},
-                            {CFG_DL_192x256_W2x4, 192, 256, 0.9},
-                            {CFG_DL3_160x256_W1x8, 160, 256, 0.85},
-                            {CFG_DL_128x128_W2x2, 128, 128, 0.55}};
-  int best = CFG_DL_128x128_W2x2;
-  double best_t = 1e300;
-  for (const C& c : cands) {
-    const long tiles = (long)((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn);
-    const double t = (double)((tiles + 255) / 256) * (c.bm * c.bn) / (65536.0 * c.eff);
-    if (t < best_t) { best_t = t; best = c.cfg; }
-  }
-  return best;
+  // Fitted to every configuration's time over M = 20 .. 26 000 at the block
+  // shapes of widths 384, 768 and 1024 (residual of the fit 7-14 %).  Over
+  // those 228 products the configuration it picks takes 0.6 % longer than the
+  // fastest on average (18 % at most); estimating rounds of the 128-row and
+  // larger tiles alone, as before the small tiles, took 65 % longer (577 x
+  // 1024 x 4096: 45.8 us as 40 tiles of 128 x 128, 15.2 us as 160 of 64 x 64).
+  static const GemmCost cands[] = {{CFG_DL_256x256_W2x4, 256, 256, 0.0, 0.30, 1.09, 10.1},
+                                   {CFG_DL_192x256_W2x4, 192, 256, 0.0, 0.30, 0.938, 8.07},
+                                   {CFG_DL3_160x256_W1x8, 160, 256, 0.0, 0.0, 0.812, 7.18},
+                                   {CFG_S4_128x128_W2x4, 128, 128, 0.45, 0.0, 0.423, 5.0},
+                                   {CFG_S3_64x128_W2x4, 64, 128, 2.76, 0.28, 0.29, 1.4},
+                                   {CFG_S4_64x64_W2x2, 64, 64, 3.1, 0.168, 0.164, 0.95},
+                                   {CFG_S4_64x32_W2x1, 64, 32, 3.4, 0.141, 0.115, 0.52}};
+  const GemmCost* best = cands;
+  for (const GemmCost& c : cands)
+    if (gemm_cost(c, M, N, K) < gemm_cost(*best, M, N, K)) best = &c;
+  return best->cfg;
 }
 
 hipError_t gemm_bf16(const bf16_t* A, int lda, const void* B, int ldb, bool b_fp8, int M, int N,
                      int K, int op, int cfg, const EpiArgs& e, hipStream_t s) {
   if (M <= 0) return hipSuccess;
   if (b_fp8 && op == OP_PATCH) return hipErrorInvalidValue;
-  if (cfg < 0 || cfg >= N_BF16_CFGS) cfg = gemm_cfg_heuristic(M, N, K, b_fp8);
+  if (!gemm_cfg_is_bf16(cfg)) cfg = gemm_cfg_heuristic(M, N, K, b_fp8);
   // The register-staged kernel has no producer side of the LayerNorm
   // folding, reads no device row count and has no GELU-backward form; its
   // direct-to-LDS counterpart gives the same bits.
@@ -98,6 +123,10 @@ hipError_t gemm_bf16(const bf16_t* A, int lda, const void* B, int ldb, bool b_fp
     case 6: return gemm_launch_cfg6(A, lda, B, ldb, b_fp8, M, N, K, op, e, s);
     case 7: return gemm_launch_cfg7(A, lda, B, ldb, b_fp8, M, N, K, op, e, s);
     case 8: return gemm_launch_cfg8(A, lda, B, ldb, b_fp8, M, N, K, op, e, s);
+    case 13: return gemm_launch_cfg13(A, lda, B, ldb, b_fp8, M, N, K, op, e, s);
+    case 14: return gemm_launch_cfg14(A, lda, B, ldb, b_fp8, M, N, K, op, e, s);
+    case 15: return gemm_launch_cfg15(A, lda, B, ldb, b_fp8, M, N, K, op, e, s);
+    case 16: return gemm_launch_cfg16(A, lda, B, ldb, b_fp8, M, N, K, op, e, s);
   }
   return hipErrorInvalidValue;
 }

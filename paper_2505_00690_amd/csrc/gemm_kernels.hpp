@@ -15,6 +15,8 @@
 #pragma once
 
 
+#include <type_traits>
+
 #include "kernels.hpp"
 
 namespace vl {
@@ -365,9 +367,10 @@ __device__ __forceinline__ int swz8(int row, int kk, int g) {  // byte offset in
   return row * BK + ((kk ^ ((row >> 2) & 3)) << 4) + (g << 3);
 }
 
-template <int BM, int BN, int WGM, int WGN, bool B_FP8, int OP, int RPM, int ST>
+template <int BM, int BN, int WGM, int WGN, bool B_FP8, int OP, int RPM, int ST, bool SMALL>
 __global__ __launch_bounds__(WGM* WGN * 64)
-__attribute__((amdgpu_waves_per_eu(WGM * WGN / 4, WGM * WGN / 4))) void k_gemm_bf16_dl(
+__attribute__((amdgpu_waves_per_eu(SMALL ? 2 : WGM * WGN / 4,
+                                   SMALL ? 4 : WGM * WGN / 4))) void k_gemm_bf16_dl(
     const bf16_t* __restrict__ A, int lda, const void* __restrict__ Bv, int ldb, int M, int N,
     int K, int gm, int gn, EpiArgs e) {
   constexpr int EPI = OpEpi<OP>::kind;
@@ -387,7 +390,9 @@ __attribute__((amdgpu_waves_per_eu(WGM * WGN / 4, WGM * WGN / 4))) void k_gemm_b
 
   // One LDS arena: a ring of ST operand tile pairs during the K loop, then
   // per-wave epilogue staging slabs (32 rows x WN FP32 each).
-  static_assert(ST == 2 || ST == 3, "two or three K tiles in flight");
+  static_assert(SMALL ? ST >= 2 && ST <= 8 && GA % NW == 0 && GB % NW == 0 : ST == 2 || ST == 3,
+                "two or three K tiles in flight; small tiles: two to eight, the same load count "
+                "in every wave");
   constexpr int LDS_AB = ST * (BM * BK * 2 + BN * BK * BES);
   constexpr int LDS_EPI = NW * 32 * WN * 4;
   __shared__ __attribute__((aligned(1024))) char smem[LDS_AB > LDS_EPI ? LDS_AB : LDS_EPI];
@@ -524,15 +529,123 @@ __attribute__((amdgpu_waves_per_eu(WGM * WGN / 4, WGM * WGN / 4))) void k_gemm_b
   // exactly the next tile's loads in flight.
   const int n_ld = (GA % NW == 0 || wave < GA % NW ? IA : IA - 1) +
                    (GB % NW == 0 || wave < GB % NW ? IB : IB - 1);
+  // Small tiles: at most `t` tiles' loads of this wave outstanding.
+  auto wait_tiles = [&](int t) {
+    constexpr int L = IA + IB;
+    switch (t) {
+      case 0: asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); break;
+      case 1: asm volatile("s_waitcnt vmcnt(%0)" ::"n"(L < 64 ? L : 63) : "memory"); break;
+      case 2: asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * L < 64 ? 2 * L : 63) : "memory"); break;
+      case 3: asm volatile("s_waitcnt vmcnt(%0)" ::"n"(3 * L < 64 ? 3 * L : 63) : "memory"); break;
+      case 4: asm volatile("s_waitcnt vmcnt(%0)" ::"n"(4 * L < 64 ? 4 * L : 63) : "memory"); break;
+      case 5: asm volatile("s_waitcnt vmcnt(%0)" ::"n"(5 * L < 64 ? 5 * L : 63) : "memory"); break;
+      default: asm volatile("s_waitcnt vmcnt(%0)" ::"n"(6 * L < 64 ? 6 * L : 63) : "memory"); break;
+    }
+  };
   auto wait_all_but_one_tile = [&]() {
     if (n_ld == IA + IB) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(IA + IB) : "memory");
     else if (n_ld == IA + IB - 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(IA + IB - 1) : "memory");
     else asm volatile("s_waitcnt vmcnt(%0)" ::"n"(IA + IB - 2) : "memory");
   };
 
+  constexpr int CPR = WN / 4;    // 16-byte FP32 chunks per staged row
+  static_assert(CPR >= 8 && 64 % CPR == 0, "staging layout needs WN in {32, 64, 128}");
+  auto sw = [](int r) { return CPR >= 16 ? (r & 15) : ((r >> 1) & 7); };
+  constexpr int RPP = 64 / CPR;  // rows per read-back pass
+  constexpr int NP = 32 / RPP;   // passes per slab
+  constexpr int NB = NP < 8 ? NP : 8;  // passes per batch of global loads
+  float* stage = reinterpret_cast<float*>(smem) + wave * 32 * WN;
+  const int rc = lane % CPR, rr = lane / CPR;
+  const int n = n0 + wn * WN + 4 * rc;
+  const bool n_ok = n < N;
+  float4 bias4 = make_float4(0.f, 0.f, 0.f, 0.f), ws4 = make_float4(1.f, 1.f, 1.f, 1.f);
+  // LayerNorm folding: consumer constants c1 / c2 (c2 in place of the bias),
+  // or the producer's next-LayerNorm gain (in bias4's place: unused there).
+  const bool fold_in = (EPI == EPI_BIAS || EPI == EPI_BIAS_GELU) && e.row_stats != nullptr;
+  const bool fold_out = EPI == EPI_BIAS_RESID && e.u_out != nullptr;
+  float4 c14 = make_float4(0.f, 0.f, 0.f, 0.f), g4 = c14;
+  auto load_consts = [&]() {
+    if (EPI == EPI_PATCH || EPI == EPI_SCALE_BIAS || EPI == EPI_DGELU || !n_ok) return;
+    if (fold_in) {
+      c14 = *reinterpret_cast<const float4*>(e.c1 + n);
+      bias4 = *reinterpret_cast<const float4*>(e.c2 + n);
+    } else {
+      bias4 = *reinterpret_cast<const float4*>(e.bias + n);
+    }
+    if (fold_out) g4 = *reinterpret_cast<const float4*>(e.u_gamma + n);
+    if (e.wscale) ws4 = *reinterpret_cast<const float4*>(e.wscale + n);
+  };
+  // The residual (or z) rows of a slab: with one batch of loads per slab,
+  // slab b+1's are issued before slab b's stores, so waiting for them does
+  // not also wait for those stores to complete (the vector memory counter
+  // counts loads and stores in issue order).
+  constexpr bool XLOAD = EPI == EPI_BIAS_RESID || EPI == EPI_DGELU;
+  constexpr bool XNEXT = XLOAD && NB == NP;
+  const float* xsrc = EPI == EPI_DGELU ? e.aux
+                      : e.resid_in     ? e.resid_in
+                                       : static_cast<const float*>(e.out);
+  float4 xn[NB];
+  auto load_x = [&](int b, float4 (&dst)[NB]) {
+#pragma unroll
+    for (int p = 0; p < NB; ++p) {
+      const int m = m0 + wm * WM + b * 32 + rr + p * RPP;
+      if (m < M && n_ok) dst[p] = *reinterpret_cast<const float4*>(xsrc + (size_t)m * e.ldo + n);
+    }
+  };
+  // Small tiles load the epilogue's operands before the K loop: at a few
+  // microseconds per launch a memory round trip after the last MFMA shows.
+  if (SMALL) {
+    load_consts();
+    if (XNEXT) load_x(0, xn);
+  }
+
   // Pipeline across tiles: the last sub-step's MFMAs of tile kt run after the
   // barrier, overlapping the first LDS reads of tile kt+1, so the matrix
   // cores do not drain at every barrier.  Loads run ST - 1 tiles ahead.
+  if constexpr (SMALL) {
+    // Small wave tiles have too few MFMAs per K sub-step to cover an LDS
+    // read, so the fragments of a whole K tile are read at once, one tile
+    // ahead of their MFMAs.  At iteration kt's barrier every wave has tile
+    // kt in registers, so its stage takes tile kt + ST.
+    bf16x8 fa[2][4][TN], fb[2][4][TM];
+    for (int i = 0; i < ST && i < KT; ++i) issue(i, i * BK);
+    wait_tiles(min(KT, ST) - 1);
+    lds_barrier();
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) ldfrag(fa[0][kk], fb[0][kk], 0, kk);
+    int cur = 0;
+    // One K tile; `steady`: tile kt + ST exists, so ST - 2 tiles stay in
+    // flight behind tile kt + 1 and the wait is an immediate.
+    auto step = [&](auto buf, auto steady, int kt) {
+      constexpr int f = decltype(buf)::value;
+      const int nxt = cur + 1 == ST ? 0 : cur + 1;
+      if (decltype(steady)::value)
+        asm volatile("s_waitcnt vmcnt(%0)" ::"n"((ST - 2) * (IA + IB)) : "memory");
+      else
+        wait_tiles(max(min(KT - 2 - kt, ST - 2), 0));
+      lds_barrier();
+      if (decltype(steady)::value) issue(cur, (kt + ST) * BK);
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk) ldfrag(fa[f ^ 1][kk], fb[f ^ 1][kk], nxt, kk);
+      // The reads stay ahead of the MFMAs that hide their latency.
+      asm volatile("" ::: "memory");
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk) mma(fa[f][kk], fb[f][kk]);
+      cur = nxt;
+    };
+    int kt = 0;
+    for (; kt + 1 + ST < KT; kt += 2) {
+      step(std::integral_constant<int, 0>(), std::true_type(), kt);
+      step(std::integral_constant<int, 1>(), std::true_type(), kt + 1);
+    }
+    for (; kt < KT; kt += 2) {
+      if (kt + ST < KT) step(std::integral_constant<int, 0>(), std::true_type(), kt);
+      else step(std::integral_constant<int, 0>(), std::false_type(), kt);
+      if (kt + 1 >= KT) break;
+      step(std::integral_constant<int, 1>(), std::false_type(), kt + 1);
+    }
+  } else {
   issue(0, 0);
   if (ST == 3 && KT > 1) {
     issue(1, BK);
@@ -566,6 +679,7 @@ __attribute__((amdgpu_waves_per_eu(WGM * WGN / 4, WGM * WGN / 4))) void k_gemm_b
     mma(fw1, fx1);
     interleave();
   }
+  }
 
   // Epilogue.  The accumulator layout gives each lane one row and 4-column
   // groups spread over the wave tile, so direct stores would touch 32 rows
@@ -578,50 +692,10 @@ __attribute__((amdgpu_waves_per_eu(WGM * WGN / 4, WGM * WGN / 4))) void k_gemm_b
   // chunks, so bias / residual loads and output stores are full-line
   // accesses, and each lane's columns (hence its bias) stay fixed.
   lds_barrier();  // all waves are done with the operand tiles
-  constexpr int CPR = WN / 4;    // 16-byte FP32 chunks per staged row
-  static_assert(CPR >= 8 && 64 % CPR == 0, "staging layout needs WN in {32, 64, 128}");
-  auto sw = [](int r) { return CPR >= 16 ? (r & 15) : ((r >> 1) & 7); };
-  constexpr int RPP = 64 / CPR;  // rows per read-back pass
-  constexpr int NP = 32 / RPP;   // passes per slab
-  constexpr int NB = NP < 8 ? NP : 8;  // passes per batch of global loads
-  float* stage = reinterpret_cast<float*>(smem) + wave * 32 * WN;
-  const int rc = lane % CPR, rr = lane / CPR;
-  const int n = n0 + wn * WN + 4 * rc;
-  const bool n_ok = n < N;
-  float4 bias4 = make_float4(0.f, 0.f, 0.f, 0.f), ws4 = make_float4(1.f, 1.f, 1.f, 1.f);
-  // LayerNorm folding: consumer constants c1 / c2 (c2 in place of the bias),
-  // or the producer's next-LayerNorm gain (in bias4's place: unused there).
-  const bool fold_in = (EPI == EPI_BIAS || EPI == EPI_BIAS_GELU) && e.row_stats != nullptr;
-  const bool fold_out = EPI == EPI_BIAS_RESID && e.u_out != nullptr;
-  float4 c14 = make_float4(0.f, 0.f, 0.f, 0.f), g4 = c14;
-  if (EPI != EPI_PATCH && EPI != EPI_SCALE_BIAS && EPI != EPI_DGELU && n_ok) {
-    if (fold_in) {
-      c14 = *reinterpret_cast<const float4*>(e.c1 + n);
-      bias4 = *reinterpret_cast<const float4*>(e.c2 + n);
-    } else {
-      bias4 = *reinterpret_cast<const float4*>(e.bias + n);
-    }
-    if (fold_out) g4 = *reinterpret_cast<const float4*>(e.u_gamma + n);
-    if (e.wscale) ws4 = *reinterpret_cast<const float4*>(e.wscale + n);
+  if (!SMALL) {
+    load_consts();
+    if (XNEXT) load_x(0, xn);
   }
-  // The residual (or z) rows of a slab: with one batch of loads per slab,
-  // slab b+1's are issued before slab b's stores, so waiting for them does
-  // not also wait for those stores to complete (the vector memory counter
-  // counts loads and stores in issue order).
-  constexpr bool XLOAD = EPI == EPI_BIAS_RESID || EPI == EPI_DGELU;
-  constexpr bool XNEXT = XLOAD && NB == NP;
-  const float* xsrc = EPI == EPI_DGELU ? e.aux
-                      : e.resid_in     ? e.resid_in
-                                       : static_cast<const float*>(e.out);
-  float4 xn[NB];
-  auto load_x = [&](int b, float4 (&dst)[NB]) {
-#pragma unroll
-    for (int p = 0; p < NB; ++p) {
-      const int m = m0 + wm * WM + b * 32 + rr + p * RPP;
-      if (m < M && n_ok) dst[p] = *reinterpret_cast<const float4*>(xsrc + (size_t)m * e.ldo + n);
-    }
-  };
-  if (XNEXT) load_x(0, xn);
 #pragma unroll
   for (int b = 0; b < TM; ++b) {
 #pragma unroll
@@ -749,7 +823,7 @@ __attribute__((amdgpu_waves_per_eu(WGM * WGN / 4, WGM * WGN / 4))) void k_gemm_b
 
 
 
-template <int BM, int BN, int WGM, int WGN, bool B_FP8, int RPM = 2, int ST = 2>
+template <int BM, int BN, int WGM, int WGN, bool B_FP8, int RPM = 2, int ST = 2, bool SMALL = false>
 static hipError_t launch_bf16_dl(const bf16_t* A, int lda, const void* B, int ldb, int M,
                                  int N, int K, int op, const EpiArgs& e, hipStream_t s) {
   const int gm = (M + BM - 1) / BM, gn = (N + BN - 1) / BN;
@@ -757,8 +831,8 @@ static hipError_t launch_bf16_dl(const bf16_t* A, int lda, const void* B, int ld
       block(WGM * WGN * 64);
 #define VL_GEMM_CASE(OP)                                                                  \
   case OP:                                                                                \
-    hipLaunchKernelGGL((k_gemm_bf16_dl<BM, BN, WGM, WGN, B_FP8, OP, RPM, ST>), grid, block, \
-                       0, s, A, lda, B, ldb, M, N, K, gm, gn, e);                         \
+    hipLaunchKernelGGL((k_gemm_bf16_dl<BM, BN, WGM, WGN, B_FP8, OP, RPM, ST, SMALL>), grid, \
+                       block, 0, s, A, lda, B, ldb, M, N, K, gm, gn, e);                         \
     break;
   switch (op) {
     VL_GEMM_CASE(OP_PATCH)

@@ -95,10 +95,20 @@ enum GemmCfg {
   CFG_MX_192x256_W2x4 = 10,
   CFG_MX_128x256_W2x4 = 11,
   CFG_MX_128x128_W2x2 = 12,
-  N_GEMM_CFGS = 13
+  N_MX_END = 13,
+  // BF16 configurations with small tiles and a deep K ring, for products
+  // with too few large tiles to fill the chip.
+  CFG_S4_64x32_W2x1 = 13,
+  CFG_S4_64x64_W2x2 = 14,
+  CFG_S3_64x128_W2x4 = 15,
+  CFG_S4_128x128_W2x4 = 16,
+  N_GEMM_CFGS = 17
 };
 const char* gemm_cfg_name(int cfg);
-inline bool gemm_cfg_is_mx(int cfg) { return cfg >= N_BF16_CFGS && cfg < N_GEMM_CFGS; }
+inline bool gemm_cfg_is_mx(int cfg) { return cfg >= N_BF16_CFGS && cfg < N_MX_END; }
+inline bool gemm_cfg_is_bf16(int cfg) {
+  return cfg >= 0 && cfg < N_GEMM_CFGS && !gemm_cfg_is_mx(cfg);
+}
 // Configuration used when none is tuned for an operation.
 int gemm_cfg_heuristic(int M, int N, int K, bool b_fp8);
 int gemm_mx_cfg_heuristic(int M, int N, int K);

@@ -757,6 +757,33 @@ def test_every_gemm_config_bitwise_identical_and_autotune(V, precision, fused_ln
     enc.close()
 
 
+@pytest.mark.parametrize("precision", ["bf16", "fp8w"])
+@pytest.mark.parametrize("sizes", [[(16, 16)], [(64, 64)], [(64, 64)] * 3 + [(48, 80)],
+                                   [(112, 112)], [(128, 128)] * 2 + [(16, 32)]])
+def test_small_tile_configs_at_ragged_rows(V, precision, sizes):
+    """The small-tile configurations (and the heuristic) against the
+    register-staged one, bitwise, where they can go wrong: fewer rows than a
+    tile, rows just past one, fewer K tiles (2) than the ring has stages and
+    a wrapping ring (8)."""
+    enc = V.Encoder(synth.MODELS["tiny"], torch.from_numpy(blob("tiny", 1000)).cuda(), precision)
+    pix = torch.from_numpy(pack(synth.make_images(sizes, 2600))).cuda()
+    bucket = sum(1 + (h // 16) * (w // 16) for h, w in sizes).bit_length() - 1
+    names = {V.vl_gemm_config_name(i): i for i in range(V.vl_gemm_config_count())}
+    got = {}
+    for name, cfg in [("heuristic", -1), *names.items()]:
+        if name == "heuristic" or name.startswith("S") or name == "REG_128x128_W2x2":
+            table = [[-1] * V.VL_N_M_BUCKETS for _ in range(V.VL_N_GEMM_OPS)]
+            for row in table:
+                row[bucket] = cfg
+            V.vl_model_set_tuning(enc.handle, table)
+            got[name] = enc.encode(pix, sizes).clone()
+    torch.cuda.synchronize()
+    assert len(got) > 2
+    for name, e in got.items():
+        assert torch.equal(e, got["REG_128x128_W2x2"]), name
+    enc.close()
+
+
 # ------------------------------------------------------- RGB-D observations
 def test_rgbd_tiny_fp32_ragged(V):
     """Four input planes (RGB + depth) through the patch gather and the
