@@ -155,6 +155,19 @@ __device__ __forceinline__ void dma16(i32x4 rsrc, uint32_t lds, int voffset, int
                : "memory", "m0");
 }
 
+// dma16 with a wave-uniform part of the row offset (sadd) added in place, so
+// loads of many row groups share one live per-lane offset.  (Row offsets stay
+// in the vector offset, which the buffer bound checks.)
+__device__ __forceinline__ void dma16_rows(i32x4 rsrc, uint32_t lds, int voffset, int sadd,
+                                           int soffset) {
+  int t;
+  asm volatile("s_mov_b32 m0, %1\n\tv_add_u32 %0, %4, %2\n\t"
+               "buffer_load_dwordx4 %0, %3, %5 offen lds"
+               : "=&v"(t)
+               : "s"(lds), "v"(voffset), "s"(rsrc), "s"(sadd), "s"(soffset)
+               : "memory", "m0");
+}
+
 // The same with 4 bytes per lane: lane i's dword lands at LDS byte lds + 4 i.
 __device__ __forceinline__ void dma4(i32x4 rsrc, uint32_t lds, int voffset, int soffset) {
   asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dword %1, %2, %3 offen lds"

@@ -9,8 +9,8 @@ namespace vl {
 hipError_t gemm_launch_cfg15(const bf16_t* A, int lda, const void* B, int ldb, bool b_fp8,
                                int M, int N, int K, int op, const EpiArgs& e, hipStream_t s) {
   if (b_fp8)
-    return launch_bf16_dl<64, 128, 2, 4, true, 2, 3, true>(A, lda, B, ldb, M, N, K, op, e, s);
-  return launch_bf16_dl<64, 128, 2, 4, false, 2, 3, true>(A, lda, B, ldb, M, N, K, op, e, s);
+    return launch_bf16_dl<64, 128, 2, 4, true, 2, 3, LOOP_SMALL>(A, lda, B, ldb, M, N, K, op, e, s);
+  return launch_bf16_dl<64, 128, 2, 4, false, 2, 3, LOOP_SMALL>(A, lda, B, ldb, M, N, K, op, e, s);
 }
 
 }  // namespace vl

@@ -367,14 +367,19 @@ __device__ __forceinline__ int swz8(int row, int kk, int g) {  // byte offset in
   return row * BK + ((kk ^ ((row >> 2) & 3)) << 4) + (g << 3);
 }
 
-template <int BM, int BN, int WGM, int WGN, bool B_FP8, int OP, int RPM, int ST, bool SMALL>
+// Main loops: the two- or three-stage ring with interleaved sub-steps, the
+// small-tile loop, and the phased loop (each described where it stands).
+enum GemmLoop { LOOP_RING, LOOP_SMALL, LOOP_PHASED };
+
+template <int BM, int BN, int WGM, int WGN, bool B_FP8, int OP, int RPM, int ST, int LOOP>
 __global__ __launch_bounds__(WGM* WGN * 64)
-__attribute__((amdgpu_waves_per_eu(SMALL ? 2 : WGM * WGN / 4,
-                                   SMALL ? 4 : WGM * WGN / 4))) void k_gemm_bf16_dl(
+__attribute__((amdgpu_waves_per_eu(LOOP == LOOP_SMALL ? 2 : WGM * WGN / 4,
+                                   LOOP == LOOP_SMALL ? 4 : WGM * WGN / 4))) void k_gemm_bf16_dl(
     const bf16_t* __restrict__ A, int lda, const void* __restrict__ Bv, int ldb, int M, int N,
     int K, int gm, int gn, EpiArgs e) {
   constexpr int EPI = OpEpi<OP>::kind;
   constexpr bool OUT_BF16 = OP == OP_QKV || OP == OP_FC1;
+  constexpr bool SMALL = LOOP == LOOP_SMALL;
   constexpr int NW = WGM * WGN;
   constexpr int WM = BM / WGM, WN = BN / WGN;
   constexpr int TM = WM / 32, TN = WN / 32;
@@ -418,9 +423,9 @@ __attribute__((amdgpu_waves_per_eu(SMALL ? 2 : WGM * WGN / 4,
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / WGN, wn = wave % WGN;
 
-  const i32x4 ra = buffer_rsrc(A + (size_t)m0 * lda, (uint64_t)(M - m0) * lda * 2);
+  const i32x4 ra = buffer_rsrc(A + (size_t)m0 * lda, (uint64_t)min(M - m0, BM) * lda * 2);
   const i32x4 rb = buffer_rsrc(static_cast<const char*>(Bv) + (size_t)n0 * ldb * BES,
-                               (uint64_t)(N - n0) * ldb * BES);
+                               (uint64_t)min(N - n0, BN) * ldb * BES);
   // Lane's place inside an 8-row group g8: row 8*g8 + l/8, physical chunk
   // l%8, hence logical chunk (l%8) ^ f(row) = (l%8) ^ (l/8) ^ (g8%8).
   const int lrow = lane >> 3, lchunk = (lane & 7) ^ (lane >> 3);
@@ -464,43 +469,45 @@ __attribute__((amdgpu_waves_per_eu(SMALL ? 2 : WGM * WGN / 4,
   // swizzle and the lane's half g folded in: BF16 chunk (2kk + g) ^ f(row)
   // of a 128-byte row is (offset ^ (kk << 5)); e4m3 chunk kk ^ f8(row) of a
   // 64-byte row is (offset ^ (kk << 4)).
-  // Row r0 + 32b has the chunk permutation of row r0 + 32 (b & 1) (the
-  // swizzles depend on the row modulo 64), so the offset of fragment b is
-  // one of two per-lane bases plus an immediate of 32b rows: two live
-  // registers per operand instead of one per fragment.
-  int pA[2], pB[2];
-#pragma unroll
-  for (int j = 0; j < 2; ++j) {
-    const int ra = wm * WM + j * 32 + l32, rb = wn * WN + j * 32 + l32;
-    pA[j] = (wm * WM + l32) * (BK * 2) + ((g ^ swz_f(ra)) << 4);
-    pB[j] = B_FP8 ? (wn * WN + l32) * BK + (((rb >> 2) & 3) << 4) + (g << 3)
-                  : (wn * WN + l32) * (BK * 2) + ((g ^ swz_f(rb)) << 4);
+  // Row r0 + 32b has the chunk permutation of row r0 with bit 2 of the chunk
+  // flipped when b is odd, which for BF16 is sub-step kk ^ 2 of row r0 (e4m3:
+  // the permutation of row r0): the offset of fragment (kk, b) is one of four
+  // per-lane bases plus an immediate of 32b rows.
+  int pA, pB;
+  {
+    const int ra = wm * WM + l32, rb = wn * WN + l32;
+    pA = ra * (BK * 2) + ((g ^ swz_f(ra)) << 4);
+    pB = B_FP8 ? rb * BK + (((rb >> 2) & 3) << 4) + (g << 3)
+               : rb * (BK * 2) + ((g ^ swz_f(rb)) << 4);
   }
   bf16x8 fw0[TN], fx0[TM], fw1[TN], fx1[TM];
-  auto ldfrag = [&](bf16x8* fw, bf16x8* fx, int buf, int kk) {
-    const char* tA = reinterpret_cast<const char*>(sA[buf]);
+  auto ldB = [&](int buf, int kk, int a) {
     const char* tB = reinterpret_cast<const char*>(sB[buf]);
-#pragma unroll
-    for (int a = 0; a < TN; ++a) {
-      if (B_FP8) {
-        const u32x2 c8 =
-            *reinterpret_cast<const u32x2*>(tB + (pB[a & 1] ^ (kk << 4)) + a * 32 * BK);
-        typedef __bf16 b2 __attribute__((ext_vector_type(2)));
-        const b2 h0 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(c8.x, 1.0f, false);
-        const b2 h1 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(c8.x, 1.0f, true);
-        const b2 h2 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(c8.y, 1.0f, false);
-        const b2 h3 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(c8.y, 1.0f, true);
-        bf16x8 f;
-        f[0] = h0[0]; f[1] = h0[1]; f[2] = h1[0]; f[3] = h1[1];
-        f[4] = h2[0]; f[5] = h2[1]; f[6] = h3[0]; f[7] = h3[1];
-        fw[a] = f;
-      } else {
-        fw[a] = *reinterpret_cast<const bf16x8*>(tB + (pB[a & 1] ^ (kk << 5)) + a * 32 * BK * 2);
-      }
+    if (B_FP8) {
+      const u32x2 c8 = *reinterpret_cast<const u32x2*>(tB + (pB ^ (kk << 4)) + a * 32 * BK);
+      typedef __bf16 b2 __attribute__((ext_vector_type(2)));
+      const b2 h0 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(c8.x, 1.0f, false);
+      const b2 h1 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(c8.x, 1.0f, true);
+      const b2 h2 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(c8.y, 1.0f, false);
+      const b2 h3 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(c8.y, 1.0f, true);
+      bf16x8 f;
+      f[0] = h0[0]; f[1] = h0[1]; f[2] = h1[0]; f[3] = h1[1];
+      f[4] = h2[0]; f[5] = h2[1]; f[6] = h3[0]; f[7] = h3[1];
+      return f;
     }
+    return *reinterpret_cast<const bf16x8*>(tB + (pB ^ ((kk ^ 2 * (a & 1)) << 5)) +
+                                            a * 32 * BK * 2);
+  };
+  auto ldA = [&](int buf, int kk, int b) {
+    const char* tA = reinterpret_cast<const char*>(sA[buf]);
+    return *reinterpret_cast<const bf16x8*>(tA + (pA ^ ((kk ^ 2 * (b & 1)) << 5)) +
+                                            b * 32 * BK * 2);
+  };
+  auto ldfrag = [&](bf16x8* fw, bf16x8* fx, int buf, int kk) {
 #pragma unroll
-    for (int b = 0; b < TM; ++b)
-      fx[b] = *reinterpret_cast<const bf16x8*>(tA + (pA[b & 1] ^ (kk << 5)) + b * 32 * BK * 2);
+    for (int a = 0; a < TN; ++a) fw[a] = ldB(buf, kk, a);
+#pragma unroll
+    for (int b = 0; b < TM; ++b) fx[b] = ldA(buf, kk, b);
   };
   auto mma = [&](const bf16x8* fw, const bf16x8* fx) {
 #pragma unroll
@@ -645,6 +652,122 @@ __attribute__((amdgpu_waves_per_eu(SMALL ? 2 : WGM * WGN / 4,
       if (kt + 1 >= KT) break;
       step(std::integral_constant<int, 1>(), std::false_type(), kt + 1);
     }
+  } else if constexpr (LOOP == LOOP_PHASED) {
+    // With two whole-tile stages a tile's loads have one tile's time to
+    // land, which a full chip's L2 traffic exceeds.  Here a tile is loaded in
+    // two portions, P (B and each wave's first TM0 row blocks of A) and Q
+    // (its other row blocks), and computed in four phases,
+    //   A0 Bx | A0 By | A1 By | A1 Bx     (Bx, By: the two column blocks)
+    // so that P's stage is free after phase 0 and Q's after phase 2: each
+    // portion's loads for tile t + 2 are issued then and have one and a half
+    // tiles to land.  Fragments are read a phase ahead of their MFMAs (the
+    // next tile's A0 and first B during phase 3, into the registers of By,
+    // which then is the next tile's Bx).  Every accumulator still takes its
+    // K steps in order.
+    static_assert(ST == 2 && TN == 2 && TM % 2 == 0, "phased loop: wave tile in quarters");
+    constexpr int TM0 = TM / 2;
+    constexpr int GP = WGM * TM0 * 4, GQ = GP;   // 8-row groups of A in P and Q
+    static_assert(GP % NW == 0 && GQ % NW == 0 && GB % NW == 0, "row groups / waves");
+    constexpr int NP_ = GP / NW + IB, NQ_ = GQ / NW;        // loads per wave
+    static_assert(NW == 8 && TM0 % 2 == 0 && WM % 64 == 0,
+                  "every load of a wave fills row groups of one residue modulo 8");
+    const int av = a_off + ((lchunk ^ wave) << 4);
+    const int bv = b_off + (B_FP8 ? 0 : ((lchunk ^ wave) << 4));
+    // One load of P (i < NP_: A's groups, then B's) or Q of the tile at K
+    // column k0; past the last tile the row offset goes out of the buffer's
+    // bounds, so the load still counts but only writes zeros to its stage.
+    constexpr int PA_ = GP / NW;
+    const int k_end = K, oob = 0x7fffff00;
+    auto loadP = [&](int i, int buf, int k0) {
+      if (i < PA_) {
+        const int j = wave + i * NW, grp = j / (TM0 * 4) * (WM / 8) + j % (TM0 * 4);
+        dma16_rows(ra, ldsA + (buf * BM * BK + grp * 8 * BK) * 2, av,
+                   k0 < k_end ? grp * 8 * lda * 2 : oob, k0 * 2);
+      } else {
+        const int grp = wave + (i - PA_) * NW;
+        dma16_rows(rb, ldsB + (buf * BN * BK + grp * BROWS * BK) * BES, bv,
+                   k0 < k_end ? grp * BROWS * ldb * BES : oob, k0 * BES);
+      }
+    };
+    auto loadQ = [&](int i, int buf, int k0) {
+      const int j = wave + i * NW, grp = j / (TM0 * 4) * (WM / 8) + TM0 * 4 + j % (TM0 * 4);
+      dma16_rows(ra, ldsA + (buf * BM * BK + grp * 8 * BK) * 2, av,
+                 k0 < k_end ? grp * 8 * lda * 2 : oob, k0 * 2);
+    };
+    // One set of A fragments: those of the next row block half replace each
+    // K step's after its last MFMA.
+    bf16x8 af[4][TM0], bq[2][4];   // bq[j]: column block j
+    auto rdB = [&](int buf, int j) {
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk) bq[j][kk] = ldB(buf, kk, j);
+    };
+    auto mm = [&](int kk, int j, int b0) {
+#pragma unroll
+      for (int b = 0; b < TM0; ++b)
+        acc[j][b0 + b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bq[j][kk], af[kk][b],
+                                                                acc[j][b0 + b], 0, 0, 0);
+    };
+    auto rdA = [&](int buf, int kk, int b0) {
+#pragma unroll
+      for (int b = 0; b < TM0; ++b) af[kk][b] = ldA(buf, kk, b0 + b);
+    };
+    auto tile = [&](auto xb, int t) {
+      constexpr int x = decltype(xb)::value, y = x ^ 1;   // x = t & 1: stage and first B block
+      const int k2 = (t + 2) * BK;
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk) {
+        bq[y][kk] = ldB(x, kk, y);
+        mm(kk, x, 0);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      // Q of this tile has landed (the next tile's loads may be in flight),
+      // and every wave has read all of P.
+      asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NP_ + NQ_) : "memory");
+      lds_barrier();
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk) {   // P's loads ride between the MFMAs
+        mm(kk, y, 0);
+        rdA(x, kk, TM0);
+#pragma unroll
+        for (int i = 0; i < NP_; ++i)
+          if (i % 4 == kk) loadP(i, x, k2);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk) mm(kk, y, TM0);
+      __builtin_amdgcn_sched_barrier(0);
+      // P of the next tile has landed, and every wave has read Q.  (On the
+      // last tile the reads below fetch stale fragments, never used.)
+      asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NP_ + NQ_) : "memory");
+      lds_barrier();
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk) {
+        mm(kk, x, TM0);
+        bq[y][kk] = ldB(y, kk, y);
+        rdA(y, kk, 0);
+        if (kk < NQ_) loadQ(kk, x, k2);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    };
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+#pragma unroll
+      for (int i = 0; i < NP_; ++i) loadP(i, u, u * BK);
+#pragma unroll
+      for (int i = 0; i < NQ_; ++i) loadQ(i, u, u * BK);
+    }
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NP_ + 2 * NQ_) : "memory");
+    lds_barrier();
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) rdA(0, kk, 0);
+    rdB(0, 0);
+    for (int t = 0; t < KT; t += 2) {   // KT is even (the launcher's rule)
+      tile(std::integral_constant<int, 0>(), t);
+      tile(std::integral_constant<int, 1>(), t + 1);
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the zero fills past the last tile
   } else {
   issue(0, 0);
   if (ST == 3 && KT > 1) {
@@ -823,15 +946,26 @@ __attribute__((amdgpu_waves_per_eu(SMALL ? 2 : WGM * WGN / 4,
 
 
 
-template <int BM, int BN, int WGM, int WGN, bool B_FP8, int RPM = 2, int ST = 2, bool SMALL = false>
+template <int BM, int BN, int WGM, int WGN, bool B_FP8, int RPM = 2, int ST = 2,
+          int LOOP = LOOP_RING>
 static hipError_t launch_bf16_dl(const bf16_t* A, int lda, const void* B, int ldb, int M,
                                  int N, int K, int op, const EpiArgs& e, hipStream_t s) {
+  // The phased loop takes its K tiles in pairs (of every split).  It pays
+  // where the K loop is most of a tile: 256 x 256 tiles of one round on all
+  // CUs run up to 16 % faster (49 000 x 768 x 3072: 298 -> 256 us,
+  // 9232 x 1024 x 4096: 96 -> 81); at K = 1024 prologue and epilogue are 40 %
+  // of a tile and the two loops differ by less than 1 % either way.
+  const bool split = op == OP_LOGITS && e.kc > 0;
+  const int k1 = split && e.kc < K ? e.kc : K;
+  if constexpr (LOOP == LOOP_PHASED)
+    if (K % (2 * BK) || k1 % (2 * BK) || k1 < 24 * BK)
+      return launch_bf16_dl<BM, BN, WGM, WGN, B_FP8, RPM, ST, LOOP_RING>(A, lda, B, ldb, M, N, K,
+                                                                        op, e, s);
   const int gm = (M + BM - 1) / BM, gn = (N + BN - 1) / BN;
-  dim3 grid(gm * gn, op == OP_LOGITS && e.kc > 0 ? (K + e.kc - 1) / e.kc : 1),
-      block(WGM * WGN * 64);
+  dim3 grid(gm * gn, split ? (K + e.kc - 1) / e.kc : 1), block(WGM * WGN * 64);
 #define VL_GEMM_CASE(OP)                                                                  \
   case OP:                                                                                \
-    hipLaunchKernelGGL((k_gemm_bf16_dl<BM, BN, WGM, WGN, B_FP8, OP, RPM, ST, SMALL>), grid, \
+    hipLaunchKernelGGL((k_gemm_bf16_dl<BM, BN, WGM, WGN, B_FP8, OP, RPM, ST, LOOP>), grid, \
                        block, 0, s, A, lda, B, ldb, M, N, K, gm, gn, e);                         \
     break;
   switch (op) {
