@@ -13,9 +13,9 @@
 // configurations accumulate K in the same order, so they agree bitwise; the
 // per-configuration instantiations live in gemm_cfg*.hip / gemm_mx_cfg*.hip.
 //
-// FP32 path: LDS-tiled FMA kernel (64 x 64 tile, 4 x 4 per thread), the plain
-// FP32 baseline; and a few-rows FP32 kernel for the heads' small products
-// (pooled rows or embeddings against the projection or the texts).
+// FP32: the large products are in gemm_f32.hip; here a few-rows kernel for
+// the heads' small products (pooled rows or embeddings against the projection
+// or the texts).
 #include <algorithm>
 
 #include "gemm_kernels.hpp"
@@ -162,84 +162,6 @@ hipError_t gemm_mx(const uint8_t* A, const uint8_t* SA, const uint8_t* B, const 
     case CFG_MX_128x128_W2x2: return gemm_mx_launch_cfg12(A, SA, B, SB, M, N, K, op, e, s);
   }
   return hipErrorInvalidValue;
-}
-
-// ------------------------------------------------------------ FP32 FMA GEMM
-template <int OP>
-__global__ __launch_bounds__(256) void k_gemm_f32(const float* __restrict__ A, int lda,
-                                                  const float* __restrict__ B, int ldb, int M,
-                                                  int N, int K, EpiArgs e) {
-  constexpr int EPI = OpEpi<OP>::kind;
-  constexpr int T = 64, KS = 16;
-  __shared__ float sA[2][KS][T + 4];
-  __shared__ float sB[2][KS][T + 4];
-  const int tid = threadIdx.x;
-  const int m0 = blockIdx.x * T, n0 = blockIdx.y * T;
-  // loader: row = tid / 4, k4 = (tid % 4) * 4
-  const int lrow = tid >> 2, lk = (tid & 3) * 4;
-  const float* pa = A + (size_t)min(m0 + lrow, M - 1) * lda + lk;
-  const float* pb = B + (size_t)min(n0 + lrow, N - 1) * ldb + lk;
-  const int tm = tid >> 4, tn = tid & 15;
-  float acc[4][4] = {};
-  float4 ra = *reinterpret_cast<const float4*>(pa);
-  float4 rb = *reinterpret_cast<const float4*>(pb);
-  auto st = [&](int buf) {
-    sA[buf][lk + 0][lrow] = ra.x; sA[buf][lk + 1][lrow] = ra.y;
-    sA[buf][lk + 2][lrow] = ra.z; sA[buf][lk + 3][lrow] = ra.w;
-    sB[buf][lk + 0][lrow] = rb.x; sB[buf][lk + 1][lrow] = rb.y;
-    sB[buf][lk + 2][lrow] = rb.z; sB[buf][lk + 3][lrow] = rb.w;
-  };
-  st(0);
-  __syncthreads();
-  const int KT = K / KS;
-  for (int kt = 0; kt < KT; ++kt) {
-    const int cur = kt & 1;
-    if (kt + 1 < KT) {
-      ra = *reinterpret_cast<const float4*>(pa + (kt + 1) * KS);
-      rb = *reinterpret_cast<const float4*>(pb + (kt + 1) * KS);
-    }
-#pragma unroll
-    for (int k = 0; k < KS; ++k) {
-      const float4 a = *reinterpret_cast<const float4*>(&sA[cur][k][tm * 4]);
-      const float4 b = *reinterpret_cast<const float4*>(&sB[cur][k][tn * 4]);
-      const float av[4] = {a.x, a.y, a.z, a.w};
-      const float bv[4] = {b.x, b.y, b.z, b.w};
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(av[i], bv[j], acc[i][j]);
-    }
-    if (kt + 1 < KT) st(cur ^ 1);
-    __syncthreads();
-  }
-  const int n = n0 + tn * 4;
-  if (n >= N) return;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int m = m0 + tm * 4 + i;
-    if (m < M) epi_store4<EPI, false>(e, m, n, acc[i][0], acc[i][1], acc[i][2], acc[i][3]);
-  }
-}
-
-hipError_t gemm_f32(const float* A, int lda, const float* B, int ldb, int M, int N, int K,
-                    int op, const EpiArgs& e, hipStream_t s) {
-  if (M <= 0) return hipSuccess;
-  dim3 grid((M + 63) / 64, (N + 63) / 64), block(256);
-#define VL_GEMM_CASE(OP)                                                                    \
-  case OP:                                                                                  \
-    hipLaunchKernelGGL(k_gemm_f32<OP>, grid, block, 0, s, A, lda, B, ldb, M, N, K, e); break;
-  switch (op) {
-    VL_GEMM_CASE(OP_PATCH)
-    VL_GEMM_CASE(OP_QKV)
-    VL_GEMM_CASE(OP_OPROJ)
-    VL_GEMM_CASE(OP_FC1)
-    VL_GEMM_CASE(OP_FC2)
-    VL_GEMM_CASE(OP_LOGITS)
-    VL_GEMM_CASE(OP_FC1_PRE)
-    default: return hipErrorInvalidValue;
-  }
-#undef VL_GEMM_CASE
-  return hipGetLastError();
 }
 
 // ------------------------------------------------ FP32 GEMM with few A rows

@@ -138,7 +138,9 @@ hipError_t gemm_bf16_kmajor(const bf16_t* A, int lda, const bf16_t* B, int ldb, 
 hipError_t gemm_mx(const uint8_t* A, const uint8_t* SA, const uint8_t* B, const uint8_t* SB,
                    int M, int N, int K, int op, int cfg, const EpiArgs& e, hipStream_t s);
 
-// The same contraction in FP32 (FMA), output FP32.  K % 16 == 0, N % 4 == 0.
+// The same contraction in FP32 (each output one chain of fused multiply-adds
+// over ascending k, whatever the tile), output FP32.  K % 16 == 0; columns are
+// written in groups of four (up to three past an N that is no multiple).
 hipError_t gemm_f32(const float* A, int lda, const float* B, int ldb, int M, int N,
                     int K, int op, const EpiArgs& e, hipStream_t s);
 

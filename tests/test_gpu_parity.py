@@ -784,6 +784,25 @@ def test_small_tile_configs_at_ragged_rows(V, precision, sizes):
     enc.close()
 
 
+@pytest.mark.parametrize("n", [3, 40, 130, 200, 333])
+def test_fp32_tile_choice_keeps_bits(V, n):
+    """The FP32 GEMM picks its row blocks (16 to 128 rows) by the batch: every
+    image has the embedding it has alone, bitwise, and that one matches the
+    oracle."""
+    cfg = synth.MODELS["tiny"]
+    enc = V.Encoder(cfg, torch.from_numpy(blob("tiny", 1000)).cuda(), "fp32")
+    imgs = synth.make_images([(64, 64)] * n, 2700)
+    got = enc.encode(torch.from_numpy(pack(imgs)).cuda(), sizes_of(imgs))
+    ref = O.encode([imgs[0], imgs[-1]], O.weights_for(synth.blob_to_params(cfg, blob("tiny", 1000)),
+                                                     "fp32"), cfg)
+    for i, r in ((0, ref[0]), (n - 1, ref[1])):
+        alone = enc.encode(torch.from_numpy(pack([imgs[i]])).cuda(), [(64, 64)])
+        torch.cuda.synchronize()
+        assert torch.equal(alone[0], got[i])
+        assert np.linalg.norm(alone[0].cpu().numpy().astype(np.float64) - r) <= 1e-4
+    enc.close()
+
+
 # ------------------------------------------------------- RGB-D observations
 def test_rgbd_tiny_fp32_ragged(V):
     """Four input planes (RGB + depth) through the patch gather and the
