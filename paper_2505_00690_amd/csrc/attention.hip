@@ -20,8 +20,7 @@
 // exceeds it by more than 2^8 (the normaliser cancels the reference point;
 // this bounds every exponential by 2^8 and makes rescaling rare).
 //
-// FP32 kernel: one thread per query, K/V tiles of 32 tokens in LDS, online
-// softmax per tile; the plain FP32 baseline.
+// FP32 kernel: the same orientation on the FP32 matrix instruction.
 #include <type_traits>
 
 #include "kernels.hpp"
@@ -611,78 +610,167 @@ hipError_t attention_bf16_resident(const bf16_t* qkv, void* out, uint8_t* out_sc
 }
 
 // ----------------------------------------------------------------- FP32
-constexpr int F32_KV = 32;
+// FP32 throughout, on v_mfma_f32_32x32x2_f32 (an fmaf chain per output).  Four
+// waves of 32 queries; key and value tiles of 32 tokens stream through a
+// three-stage LDS ring by direct-to-LDS loads.  As in the BF16 kernel S^T = K
+// Q^T, so a lane owns one query (and 16 of a tile's 32 keys), and O^T += V^T
+// P^T takes P^T from the score registers: step r multiplies the keys 8(r/4) +
+// 4g + r%4 of the two lane halves g.  Bound by the matrix pipe (64 MFMAs of 64
+// cycles per wave and tile at head width 64; the softmax, with the library
+// exponential, is a third of that and runs beside another wave's MFMAs).
+// Measured (MI355X): eight images of 197 tokens, 12 heads of 64: 151 us with
+// one thread per query and FMAs, 26 us here.
+constexpr int F32_KV = 32;   // keys per tile
+constexpr int F32_ST = 3;    // ring stages
 
 template <int HD>
-__global__ __launch_bounds__(ATT_Q) void k_attn_f32(const float* __restrict__ qkv,
-                                                    float* __restrict__ out,
-                                                    const ImgDesc* __restrict__ imgs,
-                                                    const AttnItem* __restrict__ items,
-                                                    int heads, int causal) {
-  __shared__ float sK[F32_KV][HD];
-  __shared__ float sV[F32_KV][HD];
-  const AttnItem it = items[blockIdx.x];
-  const int h = blockIdx.y;
+__global__ __launch_bounds__(256) void k_attn_f32(const float* __restrict__ qkv,
+                                                  float* __restrict__ out,
+                                                  const ImgDesc* __restrict__ imgs,
+                                                  const AttnItem* __restrict__ items,
+                                                  int heads, int causal) {
+  constexpr int NCH = HD / 4, ROWB = HD * 4;     // 16-byte chunks, bytes per row
+  constexpr int RPI = 1024 / ROWB;               // rows per 1 KB load instruction
+  constexpr int LPW = F32_KV / RPI / 4;          // K (and V) loads per wave and tile
+  constexpr int TILE = F32_KV * ROWB, NA = HD / 32;
+  static_assert(LPW >= 1 && LPW * RPI * 4 == F32_KV, "tile / waves");
+  __shared__ __attribute__((aligned(1024))) char sK[F32_ST][TILE];
+  __shared__ __attribute__((aligned(1024))) char sV[F32_ST][TILE];
+  const int n_items = gridDim.x / heads;
+  const int wi = xcd_linear(blockIdx.x, gridDim.x);
+  const AttnItem it = items[wi % n_items];
+  const int h = wi / n_items;
   const ImgDesc dsc = imgs[it.img];
   const int N = dsc.ntok;
   const int D = heads * HD, ld = 3 * D;
   const float* base = qkv + (size_t)dsc.tok_start * ld;
-  const int tid = threadIdx.x;
-  const int q = it.q0 + tid;
-  const int qc = min(q, N - 1);
-  float qv[HD], o[HD];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l32 = lane & 31, g = lane >> 5;
+  const int qw = it.q0 + wave * 32;              // first query of this wave
+  const bool wave_active = qw < N;
+  const int q = qw + l32, qc = min(q, N - 1);
+
+  // Q operand of MFMA step s: element 2s + g of this lane's query.
+  float qf[HD / 2];
+  {
+    const float* qp = base + (size_t)qc * ld + h * HD;
 #pragma unroll
-  for (int d = 0; d < HD; d += 4) {
-    const float4 x = *reinterpret_cast<const float4*>(base + (size_t)qc * ld + h * HD + d);
-    qv[d] = x.x; qv[d + 1] = x.y; qv[d + 2] = x.z; qv[d + 3] = x.w;
-    o[d] = o[d + 1] = o[d + 2] = o[d + 3] = 0.f;
+    for (int c = 0; c < NCH; ++c) {
+      const float4 x = *reinterpret_cast<const float4*>(qp + 4 * c);
+      qf[2 * c] = g ? x.y : x.x;
+      qf[2 * c + 1] = g ? x.w : x.z;
+    }
   }
+  // Wait for Q with a wait the compiler sees, so it does not wait for it again
+  // behind the ring's loads.
+  __builtin_amdgcn_s_waitcnt(0x0F70);
+
+  // Chunk c of key row r sits at c ^ (r mod NCH), so a chunk read from 32 rows
+  // spreads over the banks; value rows 4 .. 7 of every 8 (the lane half g =
+  // 1) have their halves of 32 columns exchanged.
+  auto fv = [](int r) { return NCH == 16 ? ((r >> 2) & 1) << 3 : 0; };
+  const i32x4 rk = buffer_rsrc(base + D + h * HD, (uint64_t)N * ld * 4);
+  const i32x4 rv = buffer_rsrc(base + 2 * D + h * HD, (uint64_t)N * ld * 4);
+  int goffK[LPW], goffV[LPW];
+#pragma unroll
+  for (int i = 0; i < LPW; ++i) {
+    const int row = (wave * LPW + i) * RPI + lane / NCH, pc = lane % NCH;
+    goffK[i] = row * ld * 4 + ((pc ^ (row & (NCH - 1))) << 4);
+    goffV[i] = row * ld * 4 + ((pc ^ fv(row)) << 4);
+  }
+  const uint32_t ldsK = lds_offset(&sK[0][0]), ldsV = lds_offset(&sV[0][0]);
+  auto issue = [&](int kt, int st) {             // rows past the sequence read as zero
+    const int kb = kt * F32_KV * ld * 4;
+#pragma unroll
+    for (int i = 0; i < LPW; ++i) {
+      const uint32_t lo = st * TILE + (wave * LPW + i) * 1024;
+      dma16(rk, ldsK + lo, goffK[i] + kb, 0);
+      dma16(rv, ldsV + lo, goffV[i] + kb, 0);
+    }
+  };
+  const int kbase = l32 * ROWB + ((l32 & (NCH - 1)) << 4) + 4 * g;
+  int vbase[NA];
+#pragma unroll
+  for (int a = 0; a < NA; ++a)
+    vbase[a] = 4 * g * ROWB + 4 * l32 + 128 * (NA == 2 ? a ^ g : a);
+
   const float sc = 1.f / sqrtf((float)HD);
   float m_run = -INFINITY, l_run = 0.f;
+  f32x16 o[NA];
+#pragma unroll
+  for (int a = 0; a < NA; ++a)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) o[a][r] = 0.f;
   const int kv_end = causal ? min(N, it.q0 + ATT_Q) : N;
   const int kmax = causal ? min(N - 1, q) : N - 1;   // last key this query sees
-  for (int k0 = 0; k0 < kv_end; k0 += F32_KV) {
-    __syncthreads();
-    for (int idx = tid; idx < F32_KV * HD / 4; idx += ATT_Q) {
-      const int key = idx / (HD / 4), d = (idx % (HD / 4)) * 4;
-      const int kk = min(k0 + key, N - 1);
-      *reinterpret_cast<float4*>(&sK[key][d]) =
-          *reinterpret_cast<const float4*>(base + (size_t)kk * ld + D + h * HD + d);
-      *reinterpret_cast<float4*>(&sV[key][d]) =
-          *reinterpret_cast<const float4*>(base + (size_t)kk * ld + 2 * D + h * HD + d);
+  const int KT = (kv_end + F32_KV - 1) / F32_KV;
+  issue(0, 0);
+  if (KT > 1) issue(1, 1);
+  int st = 0;
+  for (int kt = 0; kt < KT; ++kt) {
+    if (kt + 1 < KT) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * LPW) : "memory");
+    else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    lds_barrier();
+    // The stage after next held tile kt - 1, whose readers all passed the barrier.
+    if (kt + 2 < KT) issue(kt + 2, st == 0 ? 2 : st - 1);
+    const char* tK = sK[st];
+    const char* tV = sV[st];
+    st = st == 2 ? 0 : st + 1;
+    const int k0 = kt * F32_KV;
+    // (causal: tiles after every query of the wave only keep the ring moving)
+    if (!wave_active || (causal && k0 > qw + 31)) continue;
+    f32x16 s;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) s[r] = 0.f;
+#pragma unroll
+    for (int c = 0; c < NCH; ++c) {
+      const float* kp = reinterpret_cast<const float*>(tK + (kbase ^ (c << 4)));
+      s = __builtin_amdgcn_mfma_f32_32x32x2f32(kp[0], qf[2 * c], s, 0, 0, 0);
+      s = __builtin_amdgcn_mfma_f32_32x32x2f32(kp[2], qf[2 * c + 1], s, 0, 0, 0);
     }
-    __syncthreads();
-    float s[F32_KV];
     float mt = -INFINITY;
 #pragma unroll
-    for (int j = 0; j < F32_KV; ++j) {
-      float a = 0.f;
-#pragma unroll
-      for (int d = 0; d < HD; ++d) a = fmaf(qv[d], sK[j][d], a);
-      s[j] = (k0 + j <= kmax) ? a * sc : -INFINITY;
-      mt = fmaxf(mt, s[j]);
+    for (int r = 0; r < 16; ++r) {
+      s[r] = k0 + 8 * (r >> 2) + 4 * g + (r & 3) <= kmax ? s[r] * sc : -INFINITY;
+      mt = fmaxf(mt, s[r]);
     }
+    mt = fmaxf(mt, __shfl_xor(mt, 32, 64));
+    // (key 0 is visible to every query, so the maximum is finite from the
+    // first tile on)
     const float m_new = fmaxf(m_run, mt);
-    const float alpha = expf(m_run - m_new);
-    l_run *= alpha;
+    if (__any(m_new > m_run)) {
+      const float alpha = expf(m_run - m_new);
+      l_run *= alpha;
 #pragma unroll
-    for (int d = 0; d < HD; ++d) o[d] *= alpha;
+      for (int a = 0; a < NA; ++a)
 #pragma unroll
-    for (int j = 0; j < F32_KV; ++j) {
-      const float p = expf(s[j] - m_new);
-      l_run += p;
-#pragma unroll
-      for (int d = 0; d < HD; ++d) o[d] = fmaf(p, sV[j][d], o[d]);
+        for (int r = 0; r < 16; ++r) o[a][r] *= alpha;
+      m_run = m_new;
     }
-    m_run = m_new;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      s[r] = expf(s[r] - m_run);
+      l_run += s[r];
+    }
+#pragma unroll
+    for (int r = 0; r < 16; ++r)
+#pragma unroll
+      for (int a = 0; a < NA; ++a) {
+        const float v = *reinterpret_cast<const float*>(tV + vbase[a] + (8 * (r >> 2) + (r & 3)) * ROWB);
+        o[a] = __builtin_amdgcn_mfma_f32_32x32x2f32(v, s[r], o[a], 0, 0, 0);
+      }
   }
-  if (q >= N) return;
-  const float inv = 1.f / l_run;
+  if (!wave_active || q >= N) return;
+  const float inv = 1.f / (l_run + __shfl_xor(l_run, 32, 64));
   float* op = out + (size_t)(dsc.tok_start + q) * D + h * HD;
 #pragma unroll
-  for (int d = 0; d < HD; d += 4)
-    *reinterpret_cast<float4*>(op + d) =
-        make_float4(o[d] * inv, o[d + 1] * inv, o[d + 2] * inv, o[d + 3] * inv);
+  for (int a = 0; a < NA; ++a)
+#pragma unroll
+    for (int rq = 0; rq < 4; ++rq)
+      *reinterpret_cast<float4*>(op + 32 * a + 8 * rq + 4 * g) =
+          make_float4(o[a][4 * rq] * inv, o[a][4 * rq + 1] * inv, o[a][4 * rq + 2] * inv,
+                      o[a][4 * rq + 3] * inv);
 }
 
 // ------------------------------------------------ attention pooling (MAP)
@@ -797,7 +885,7 @@ hipError_t attention_f32(const float* qkv, float* o, const ImgDesc* imgs,
                          const AttnItem* items, int n_items, int heads, int head_dim,
                          bool causal, hipStream_t s) {
   if (n_items <= 0) return hipSuccess;
-  dim3 grid(n_items, heads), block(ATT_Q);
+  dim3 grid(n_items * heads), block(256);
   if (head_dim == 64)
     hipLaunchKernelGGL(k_attn_f32<64>, grid, block, 0, s, qkv, o, imgs, items, heads,
                        (int)causal);

@@ -233,3 +233,16 @@ def test_plain_inputs_match(V):
         got = _run(V, qkv, lengths, heads, d, False, dtype)
         tol = f * (mag + (np.abs(ref) if dtype == "bf16" else 0.0)) + 1e-30
         assert np.all(np.abs(got - ref) <= tol), dtype
+
+
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("d", [64, 32])
+def test_fp32_tile_edges(V, d, causal):
+    """The FP32 kernel around its 32-key tiles, 32-query waves and 128-query
+    workgroups, within the FP32 bar (1e-4 of sum_j p_j |v_j|)."""
+    rng = np.random.Generator(np.random.PCG64(77 + d))
+    lengths, heads = [1, 2, 31, 32, 33, 63, 64, 65, 96, 97, 127, 128, 129, 161], 3
+    x = _qkv(lengths, heads, d, rng).astype(np.float32).astype(np.float64)
+    ref, mag, _, _ = oracle_attention(x, lengths, heads, d, causal)
+    got = _run(V, x, lengths, heads, d, causal, "fp32")
+    assert np.all(np.abs(got - ref) <= 1e-4 * mag)
