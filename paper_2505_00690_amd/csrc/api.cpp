@@ -1651,7 +1651,6 @@ vl_status vl_attention_backward(const void* qkv, const void* out, const float* d
   }
   const bool bf = prec == VL_BF16;
   bf16_t* dob = reinterpret_cast<bf16_t*>(w + bp.off_dob);
-  if (bf) VL_HIP(convert_bf16(d_out, dob, (size_t)bp.T * heads * head_dim, s));
   VL_HIP(attention_backward(qkv, out, bf, d_out, reinterpret_cast<const ImgDesc*>(w),
                             reinterpret_cast<const AttnItem*>(w + bp.off_items64), bp.n_items64,
                             reinterpret_cast<const AttnItem*>(w + bp.off_items128),
@@ -2562,7 +2561,7 @@ vl_status run_backward_body(vl_model* m, const TrainPlan& tp, const float* pix, 
                               m->heads, m->hd, dZ,
                               reinterpret_cast<float*>(ws + (bf ? sv.lse : tp.lse)),
                               reinterpret_cast<float*>(ws + tp.dsum), s, bf,
-                              bf ? static_cast<const bf16_t*>(dOb) : nullptr));
+                              bf ? static_cast<bf16_t*>(dOb) : nullptr));
     if ((st = rec(kEvDzQkv, s)) != VL_OK) return st;
     // ---- QKV: [q|k|v] = y1 Wqkv^T + bqkv
     const void* Wqt = bf ? static_cast<const void*>(wl + wo.qkv) : Wt;            // [D, 3D]

@@ -619,7 +619,7 @@ hipError_t attention_bf16_resident(const bf16_t* qkv, void* out, uint8_t* out_sc
 // cycles per wave and tile at head width 64; the softmax, with the library
 // exponential, is a third of that and runs beside another wave's MFMAs).
 // Measured (MI355X): eight images of 197 tokens, 12 heads of 64: 151 us with
-// one thread per query and FMAs, 26 us here.
+// one thread per query and FMAs, 29 us here.
 constexpr int F32_KV = 32;   // keys per tile
 constexpr int F32_ST = 3;    // ring stages
 

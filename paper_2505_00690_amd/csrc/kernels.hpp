@@ -289,7 +289,7 @@ hipError_t attention_backward(const void* qkv, const void* o, bool bf16, const f
                               const ImgDesc* imgs, const AttnItem* items64, int n_items,
                               const AttnItem* items128, int n_items128, int heads, int head_dim,
                               void* dqkv, float* lse, float* dsum, hipStream_t s,
-                              bool lse_given = false, const bf16_t* dO_bf16 = nullptr);
+                              bool lse_given = false, bf16_t* dO_bf16 = nullptr);
 // Pooling head: de, z [n, *] scratch, the class rows of dX, and the
 // gradients of the projection and the final LayerNorm (pg, pb [n, D] and
 // part [ceil(n / kColRows), D] scratch).

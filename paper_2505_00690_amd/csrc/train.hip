@@ -703,8 +703,9 @@ constexpr int BWD_ST = 3;    // key / value tile ring stages of the dQ kernel
 // key tile.  Work items are dealt XCD by XCD (the query blocks of one
 // (image, head) share its keys and values in one L2).  LSE_IN: lse2_io holds
 // each query's log-sum-exp (log2 units, from the forward) and is only read;
-// otherwise a first pass over the keys forms and writes it.  Also writes D =
-// rowsum(dO O) per query.
+// otherwise the same pass over the keys forms and writes it (measured at 32 x
+// 577 tokens, 16 heads of 64: 235 us with a separate pass for it, 158 us so).
+// Also writes D = rowsum(dO O) per query and, with dob_out, dO in BF16.
 template <int HD, bool LSE_IN>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k_attn_bwd_dq_mfma(const bf16_t* __restrict__ qkv,
                                                           const bf16_t* __restrict__ o,
@@ -713,7 +714,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
                                                           const AttnItem* __restrict__ items,
                                                           int heads, bf16_t* __restrict__ dqkv,
                                                           float* __restrict__ lse2_io,
-                                                          float* __restrict__ dsum_out) {
+                                                          float* __restrict__ dsum_out,
+                                                          bf16_t* __restrict__ dob_out) {
   using TK = TrTile<HD>;
   using TV = RowTile<HD>;
   constexpr int NC = HD / 16, NA = HD / 32;
@@ -754,47 +756,18 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
   }
   dsv += __shfl_xor(dsv, 32, 64);
   const float sl2 = 1.4426950408889634f / sqrtf((float)HD);
-  // pass 1 (no log-sum-exp given): each query's log-sum-exp of its scaled
-  // scores (log2 units), key fragments straight from global memory
-  float lse2;
-  if constexpr (LSE_IN) {
-    lse2 = lse2_io[qrow * heads + h];
-  } else {
-    float m = -INFINITY, l = 0.f;
-    for (int k0 = 0; k0 < N; k0 += 64) {
-      f32x16 s[2];
+  if (dob_out && qok) {   // this head's columns of dO in BF16, for the dK/dV kernel
 #pragma unroll
-      for (int kb = 0; kb < 2; ++kb) {
-#pragma unroll
-        for (int r = 0; r < 16; ++r) s[kb][r] = 0.f;
-#pragma unroll
-        for (int c = 0; c < NC; ++c) {
-          const bf16x8 kf = *reinterpret_cast<const bf16x8*>(
-              base + DM + (size_t)min(k0 + 32 * kb + l32, N - 1) * ld3 + 16 * c + 8 * g);
-          s[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[c], s[kb], 0, 0, 0);
-        }
-      }
-      float mt = -INFINITY;
-#pragma unroll
-      for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int key = k0 + 32 * kb + 8 * (r >> 2) + 4 * g + (r & 3);
-          s[kb][r] = key < N ? s[kb][r] * sl2 : -INFINITY;
-          mt = fmaxf(mt, s[kb][r]);
-        }
-      mt = fmaxf(mt, __shfl_xor(mt, 32, 64));
-      const float mn = fmaxf(m, mt);
-      float ts = 0.f;
-#pragma unroll
-      for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) ts += exp2f(s[kb][r] - mn);
-      l = l * exp2f(m - mn) + ts;
-      m = mn;
-    }
-    lse2 = m + log2f(l + __shfl_xor(l, 32, 64));
+    for (int c = 0; c < NC; ++c)
+      *reinterpret_cast<bf16x8*>(dob_out + qrow * DM + h * HD + 16 * c + 8 * g) = df[c];
   }
+  // LSE_IN: the reference is the log-sum-exp itself, p the probabilities.
+  // Otherwise a running reference, raised when a score exceeds it by more than
+  // 2^8 (as in the forward), with the sum l of the exponentials beside dQ: both
+  // are linear in p, so dQ / l is the result and log2 l + reference the
+  // log-sum-exp.
+  float ref = -INFINITY, lsum = 0.f;
+  if (LSE_IN) ref = lse2_io[qrow * heads + h];
   // Wait for the operands above with a wait the compiler sees, so its
   // wait-count pass does not hold the ring's loads back for them later.
   __builtin_amdgcn_s_waitcnt(0x0F70);
@@ -866,12 +839,32 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
         const bf16x8 vf = *reinterpret_cast<const bf16x8*>(tV + voff[kb][c]);
         dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, df[c], dp, 0, 0, 0);
       }
+      if constexpr (!LSE_IN) {
+        float mt = -INFINITY;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int key = k0 + 32 * kb + 8 * (r >> 2) + 4 * g + (r & 3);
+          mt = fmaxf(mt, key < N ? s[r] : -INFINITY);
+        }
+        mt = fmaxf(mt, __shfl_xor(mt, 32, 64)) * sl2;
+        if (__any(mt > ref + 8.f)) {
+          const float m_new = fmaxf(ref, mt);
+          const float alpha = __builtin_amdgcn_exp2f(ref - m_new);
+          lsum *= alpha;
+#pragma unroll
+          for (int a = 0; a < NA; ++a)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) dq[a][r] *= alpha;
+          ref = m_new;
+        }
+      }
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
         const int key = k0 + 32 * kb + 8 * (r >> 2) + 4 * g + (r & 3);
         // (a key past the image has a zero row, score 0; its p could
-        // overflow for a very negative log-sum-exp, so it is selected away)
-        const float p = key < N ? __builtin_amdgcn_exp2f(fmaf(s[r], sl2, -lse2)) : 0.f;
+        // overflow for a very negative reference, so it is selected away)
+        const float p = key < N ? __builtin_amdgcn_exp2f(fmaf(s[r], sl2, -ref)) : 0.f;
+        if (!LSE_IN) lsum += p;
         s[r] = p * (dp[r] - dsv);
       }
 #pragma unroll
@@ -893,7 +886,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
     if (kt + 2 < KT) tile(std::integral_constant<int, 2>(), kt + 2);
   }
   if (!qok) return;
-  const float scale = 1.0f / sqrtf((float)HD);
+  float scale = 1.0f / sqrtf((float)HD);
+  if (!LSE_IN) {
+    lsum += __shfl_xor(lsum, 32, 64);
+    scale /= lsum;
+  }
   const size_t row = (size_t)dsc.tok_start + q;
   bf16_t* out = dqkv + row * ld3 + h * HD;
 #pragma unroll
@@ -906,7 +903,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
       *reinterpret_cast<u32x2*>(out + a * 32 + 8 * rq + 4 * g) = pk;
     }
   if (g == 0) {
-    if (!LSE_IN) lse2_io[row * heads + h] = lse2;
+    if (!LSE_IN) lse2_io[row * heads + h] = ref + log2f(lsum);
     dsum_out[row * heads + h] = dsv;
   }
 }
@@ -1093,16 +1090,16 @@ static void launch_attn_bwd_mfma(const void* qkv, const void* o, const float* dO
                                  const ImgDesc* imgs, const AttnItem* items64, int n_items64,
                                  const AttnItem* items128, int n_items128, int heads, void* dqkv,
                                  float* lse, float* dsum, hipStream_t s, bool lse_given,
-                                 const bf16_t* dO_bf16) {
+                                 bf16_t* dO_bf16) {
   dim3 gq(n_items128 * heads), bq(256);
   if (lse_given)
     hipLaunchKernelGGL((k_attn_bwd_dq_mfma<HD, true>), gq, bq, 0, s,
                        static_cast<const bf16_t*>(qkv), static_cast<const bf16_t*>(o), dO, imgs,
-                       items128, heads, static_cast<bf16_t*>(dqkv), lse, dsum);
+                       items128, heads, static_cast<bf16_t*>(dqkv), lse, dsum, nullptr);
   else
     hipLaunchKernelGGL((k_attn_bwd_dq_mfma<HD, false>), gq, bq, 0, s,
                        static_cast<const bf16_t*>(qkv), static_cast<const bf16_t*>(o), dO, imgs,
-                       items128, heads, static_cast<bf16_t*>(dqkv), lse, dsum);
+                       items128, heads, static_cast<bf16_t*>(dqkv), lse, dsum, dO_bf16);
   hipLaunchKernelGGL(k_attn_bwd_dkv_mfma<HD>, gq, bq, 0, s, static_cast<const bf16_t*>(qkv),
                      dO_bf16, imgs, items128, heads, lse, dsum, static_cast<bf16_t*>(dqkv));
 }
@@ -1123,7 +1120,7 @@ hipError_t attention_backward(const void* qkv, const void* o, bool bf16, const f
                               const ImgDesc* imgs, const AttnItem* items64, int n_items,
                               const AttnItem* items128, int n_items128, int heads, int head_dim,
                               void* dqkv, float* lse, float* dsum, hipStream_t s, bool lse_given,
-                              const bf16_t* dO_bf16) {
+                              bf16_t* dO_bf16) {
   if (n_items <= 0) return hipSuccess;
   if ((lse_given || dO_bf16) && !bf16) return hipErrorInvalidValue;
   if (bf16 && (!dO_bf16 || !items128 || n_items128 <= 0)) return hipErrorInvalidValue;
