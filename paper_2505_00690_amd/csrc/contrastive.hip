@@ -14,157 +14,247 @@
 
 namespace vl {
 
-// Per-row log-sum-exp of L [n, ld] (first n columns).  One workgroup per row.
-__global__ __launch_bounds__(256) void k_row_lse(const float* __restrict__ L, int n, int ld,
-                                                 float* __restrict__ lse) {
-  __shared__ float red[4];
-  const float* r = L + (size_t)blockIdx.x * ld;
-  float mx = -INFINITY;
-  for (int j = threadIdx.x; j < n; j += 256) mx = fmaxf(mx, r[j]);
-  mx = wave_max(mx);
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = mx;
-  __syncthreads();
-  mx = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
-  __syncthreads();
+// The logits are walked in 64 x 64 tiles, one per workgroup (thread t: row t /
+// 4, the 16 columns from 16 (t % 4)), so a matrix of n^2 logits fills the chip
+// in both directions: 1024 pairs are 256 workgroups, where one workgroup per 64
+// columns left 240 CUs idle (97 us for the column sums alone; parts, merge and
+// gradient now take 20 us together).  Latency and
+// launches bound them: 4 MB of logits are read twice.
+constexpr int CT = 64;
+
+// Maximum and sum of exponentials (relative to that maximum) of 16 values and
+// the three other threads of the row.
+__device__ __forceinline__ float2 lse_part(const float (&v)[16]) {
+  float mx = v[0];
+#pragma unroll
+  for (int j = 1; j < 16; ++j) mx = fmaxf(mx, v[j]);
+  mx = fmaxf(mx, __shfl_xor(mx, 1, 64));
+  mx = fmaxf(mx, __shfl_xor(mx, 2, 64));
   float s = 0.f;
-  for (int j = threadIdx.x; j < n; j += 256) s += expf(r[j] - mx);
-  s = wave_sum(s);
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
-  __syncthreads();
-  if (threadIdx.x == 0) lse[blockIdx.x] = mx + logf((red[0] + red[1]) + (red[2] + red[3]));
+  if (mx > -INFINITY) {   // else no value in range (or none above -inf)
+#pragma unroll
+    for (int j = 0; j < 16; ++j) s += expf(v[j] - mx);
+  }
+  s += __shfl_xor(s, 1, 64);
+  s += __shfl_xor(s, 2, 64);
+  return make_float2(mx, s);
 }
 
-// Per-column log-sum-exp: a workgroup owns 64 columns; its 4 waves walk
-// interleaved rows (coalesced 256-byte row segments) with a running max and
-// sum each, merged at the end.
-__global__ __launch_bounds__(256) void k_col_lse(const float* __restrict__ L, int n, int ld,
-                                                 float* __restrict__ lse) {
-  __shared__ float smx[4][64], ssum[4][64];
-  const int c = blockIdx.x * 64 + (threadIdx.x & 63), g = threadIdx.x >> 6;
-  float mx = -INFINITY, s = 0.f;
-  if (c < n)
-    for (int i = g; i < n; i += 4) {
-      const float v = L[(size_t)i * ld + c];
-      if (v > mx) {
-        s = s * expf(mx - v) + 1.f;
-        mx = v;
-      } else {
-        s += expf(v - mx);
-      }
-    }
-  smx[g][threadIdx.x & 63] = mx;
-  ssum[g][threadIdx.x & 63] = s;
+// out [cols, ld_out] = in [rows, cols]^T, zero-filled past `rows` up to
+// ld_out columns: one 32 x 32 tile (tx, ty) through LDS.
+__device__ __forceinline__ void transpose_tile(const float* __restrict__ in, int rows, int cols,
+                                               float* __restrict__ out, int ld_out, int tx, int ty,
+                                               float (*t)[33]) {
+  const int r0 = ty * 32, c0 = tx * 32;
+  const int x = threadIdx.x & 31, y = threadIdx.x >> 5;   // 32 x 8
+  for (int k = y; k < 32; k += 8) {
+    const int r = r0 + k, c = c0 + x;
+    t[k][x] = (r < rows && c < cols) ? in[(size_t)r * cols + c] : 0.f;
+  }
   __syncthreads();
-  if (g == 0 && c < n) {
-    const int l = threadIdx.x;
-    const float m = fmaxf(fmaxf(smx[0][l], smx[1][l]), fmaxf(smx[2][l], smx[3][l]));
-    float t = 0.f;
-    for (int k = 0; k < 4; ++k) t += ssum[k][l] * expf(smx[k][l] - m);
-    lse[c] = m + logf(t);
+  for (int k = y; k < 32; k += 8) {
+    const int c = c0 + k, r = r0 + x;   // out row c, column r
+    if (c < cols && r < ld_out) out[(size_t)c * ld_out + r] = t[x][k];
   }
 }
 
-// Row i of G = dL/dl, in place over L (columns n..ld-1 set to zero: they are
-// the K padding of the gradient GEMMs), plus the row's contributions (loss,
-// sum_j G_ij (l_ij - bias), sum_j G_ij) in part[3i..3i+2].
+// Workgroups below nt^2: the (max, sum) of each row and column of logit tile
+// (ti, tj), rowp[tj][i] and colp[ti][j].  The others: the transposes Tt, Et
+// [dim, ld] of the embeddings that the gradient GEMMs read (they do not
+// depend on the logits and ride along).
+__global__ __launch_bounds__(256) void k_lse_parts(const float* __restrict__ L, int n, int ld,
+                                                   int nt, float2* __restrict__ rowp,
+                                                   float2* __restrict__ colp,
+                                                   const float* __restrict__ E,
+                                                   const float* __restrict__ T, int dim,
+                                                   float* __restrict__ Et,
+                                                   float* __restrict__ Tt) {
+  __shared__ float t[CT][CT + 1];
+  const int tid = threadIdx.x, r = tid >> 2, c0 = (tid & 3) * 16;
+  int b = blockIdx.x - nt * nt;
+  if (b >= 0) {
+    const int ntx = (dim + 31) / 32, nty = (ld + 31) / 32;
+    const bool second = b >= ntx * nty;
+    if (second) b -= ntx * nty;
+    transpose_tile(second ? E : T, n, dim, second ? Et : Tt, ld, b % ntx, b / ntx,
+                   reinterpret_cast<float(*)[33]>(&t[0][0]));
+    return;
+  }
+  const int ti = blockIdx.x / nt, tj = blockIdx.x % nt;
+  const int i = ti * CT + r, j0 = tj * CT + c0;
+  float v[16];
+  const float* row = L + (size_t)min(i, n - 1) * ld;
+#pragma unroll
+  for (int k = 0; k < 16; ++k) v[k] = -INFINITY;
+#pragma unroll
+  for (int k = 0; k < 16; k += 4)
+    if (i < n && j0 + k < n) {   // ld is a multiple of 16: whole groups are in the row
+      const float4 x = *reinterpret_cast<const float4*>(row + j0 + k);
+      const float xs[4] = {x.x, x.y, x.z, x.w};
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (j0 + k + e < n) v[k + e] = xs[e];
+    }
+#pragma unroll
+  for (int k = 0; k < 16; ++k) t[r][c0 + k] = v[k];
+  const float2 rp = lse_part(v);
+  if (i < n && (tid & 3) == 0) rowp[(size_t)tj * n + i] = rp;
+  __syncthreads();
+  // the same thread layout over the transposed tile
+#pragma unroll
+  for (int k = 0; k < 16; ++k) v[k] = t[c0 + k][r];
+  const float2 cp = lse_part(v);
+  const int j = tj * CT + r;
+  if (j < n && (tid & 3) == 0) colp[(size_t)ti * n + j] = cp;
+}
+
+// Log-sum-exps from the tiles' parts, in a fixed order: rows (blockIdx.y = 0;
+// also the diagonal logits, which the gradient kernel overwrites) and columns.
+__global__ __launch_bounds__(256) void k_lse_merge(const float2* __restrict__ rowp,
+                                                   const float2* __restrict__ colp, int n, int nt,
+                                                   const float* __restrict__ L, int ld,
+                                                   float* __restrict__ rlse,
+                                                   float* __restrict__ clse,
+                                                   float* __restrict__ diag) {
+  __shared__ float2 sm[4][64];
+  const int l = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int i = blockIdx.x * 64 + l;
+  const float2* p = (blockIdx.y ? colp : rowp) + min(i, n - 1);
+  float mx = -INFINITY, s = 0.f;
+  for (int k0 = w; k0 < nt; k0 += 16) {   // wave w: parts w, w + 4, ..., four loads at once
+    float2 v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      v[u] = k0 + 4 * u < nt ? p[(size_t)(k0 + 4 * u) * n] : make_float2(-INFINITY, 0.f);
+    const float m = fmaxf(mx, fmaxf(fmaxf(v[0].x, v[1].x), fmaxf(v[2].x, v[3].x)));
+    if (m > -INFINITY) {
+      s *= expf(mx - m);
+#pragma unroll
+      for (int u = 0; u < 4; ++u) s += v[u].y * expf(v[u].x - m);
+    }
+    mx = m;
+  }
+  sm[w][l] = make_float2(mx, s);
+  __syncthreads();
+  if (w != 0 || i >= n) return;
+  const float m = fmaxf(fmaxf(sm[0][l].x, sm[1][l].x), fmaxf(sm[2][l].x, sm[3][l].x));
+  s = 0.f;
+#pragma unroll
+  for (int u = 0; u < 4; ++u) s += sm[u][l].y * expf(sm[u][l].x - m);
+  (blockIdx.y ? clse : rlse)[i] = m + logf(s);
+  if (blockIdx.y == 0) diag[i] = L[(size_t)i * ld + i];
+}
+
+// G = dL/dl of logit tiles, in place over L (columns n .. ld-1 set to zero:
+// they are the K padding of the gradient GEMMs) and transposed into Gt [n,
+// ld] (zero-padded likewise), plus the workgroup's terms (loss, sum g (l -
+// bias), sum g) in part[3 blockIdx.x ..].  A workgroup walks `per` column
+// tiles of one row of tiles.
+//
+// Softmax head: g = ((p - d) + (q - d)) / 2n with p, q the row and column
+// softmax and d the identity.  Every row of p - d and every column of q - d
+// sums to zero, so sum g l is formed as sum ((p - d)(l - rlse_i) + (q - d)(l -
+// clse_j)) / 2n, whose terms are smaller.
 __global__ __launch_bounds__(256) void k_contrastive_grad(float* __restrict__ L, int n, int ld,
-                                                          int head, float bias,
+                                                          int nt, int per, int head, float bias,
                                                           const float* __restrict__ rlse,
                                                           const float* __restrict__ clse,
+                                                          float* __restrict__ Gt,
                                                           float* __restrict__ part) {
-  __shared__ float red[3][4];
-  const int i = blockIdx.x;
-  float* r = L + (size_t)i * ld;
+  __shared__ float t[CT][CT + 1];
+  __shared__ float red[4];
+  const int tid = threadIdx.x, r = tid >> 2, c0 = (tid & 3) * 16;
+  const int groups = (nt + per - 1) / per;
+  const int ti = blockIdx.x / groups, tj0 = blockIdx.x % groups * per;
+  const int i = ti * CT + r;
   const float inv_n = 1.f / (float)n;
+  const float rl = i < n ? rlse[i] : 0.f;
   float sl = 0.f, sg = 0.f, s0 = 0.f;
-  for (int j = threadIdx.x; j < n; j += 256) {
-    const float l = r[j];
-    float g;
-    if (head == 0) {
-      const float d = j == i ? 1.f : 0.f;
-      g = 0.5f * inv_n * ((expf(l - rlse[i]) - d) + (expf(l - clse[j]) - d));
-    } else {
-      const float z = j == i ? 1.f : -1.f;
-      const float u = -z * l;                 // loss term softplus(u)
-      sl += u > 0.f ? u + log1pf(expf(-u)) : log1pf(expf(u));
-      g = -z * inv_n / (1.f + expf(-u));      // -z sigmoid(u) / n
+  for (int tj = tj0; tj < min(tj0 + per, nt); ++tj) {
+    if (tj > tj0) __syncthreads();   // readers of the previous tile are done
+    const int j0 = tj * CT + c0;
+    float* row = L + (size_t)i * ld;
+#pragma unroll
+    for (int k = 0; k < 16; k += 4) {
+      float g[4] = {0.f, 0.f, 0.f, 0.f};
+      const bool in = i < n && j0 + k < ld;
+      if (in) {
+        const float4 x = *reinterpret_cast<const float4*>(row + j0 + k);
+        const float xs[4] = {x.x, x.y, x.z, x.w};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int j = j0 + k + e;
+          if (j >= n) continue;
+          const float l = xs[e];
+          if (head == 0) {
+            const float d = j == i ? 1.f : 0.f, cl = clse[j];
+            const float p = expf(l - rl) - d, q = expf(l - cl) - d;
+            g[e] = 0.5f * inv_n * (p + q);
+            sg += 0.5f * inv_n * (p * (l - rl) + q * (l - cl));
+          } else {
+            const float z = j == i ? 1.f : -1.f;
+            const float u = -z * l;                 // loss term softplus(u)
+            sl += u > 0.f ? u + log1pf(expf(-u)) : log1pf(expf(u));
+            g[e] = -z * inv_n / (1.f + expf(-u));   // -z sigmoid(u) / n
+            sg += g[e] * (l - bias);
+            s0 += g[e];
+          }
+        }
+        *reinterpret_cast<float4*>(row + j0 + k) = make_float4(g[0], g[1], g[2], g[3]);
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) t[r][c0 + k + e] = g[e];
     }
-    r[j] = g;
-    sg += g * (l - bias);
-    s0 += g;
+    __syncthreads();
+    const int j = tj * CT + r;       // row of Gt
+    if (j < n) {
+#pragma unroll
+      for (int k = 0; k < 16; k += 4) {
+        const int ic = ti * CT + c0 + k;
+        if (ic < ld)
+          *reinterpret_cast<float4*>(Gt + (size_t)j * ld + ic) =
+              make_float4(t[c0 + k][r], t[c0 + k + 1][r], t[c0 + k + 2][r], t[c0 + k + 3][r]);
+      }
+    }
   }
-  for (int j = n + threadIdx.x; j < ld; j += 256) r[j] = 0.f;
-  sl = wave_sum(sl); sg = wave_sum(sg); s0 = wave_sum(s0);
-  if ((threadIdx.x & 63) == 0) {
-    red[0][threadIdx.x >> 6] = sl; red[1][threadIdx.x >> 6] = sg; red[2][threadIdx.x >> 6] = s0;
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    part[3 * i + 0] = (red[0][0] + red[0][1]) + (red[0][2] + red[0][3]);
-    part[3 * i + 1] = (red[1][0] + red[1][1]) + (red[1][2] + red[1][3]);
-    part[3 * i + 2] = (red[2][0] + red[2][1]) + (red[2][2] + red[2][3]);
+  auto sum = [](float a, float b) { return a + b; };
+  sl = block_reduce(sl, red, sum);
+  sg = block_reduce(sg, red, sum);
+  s0 = block_reduce(s0, red, sum);
+  if (tid == 0) {
+    part[3 * blockIdx.x + 0] = sl;
+    part[3 * blockIdx.x + 1] = sg;
+    part[3 * blockIdx.x + 2] = s0;
   }
 }
 
-// Softmax-head loss terms need the diagonal logits, which the gradient
-// kernel overwrites: take them first.  diag[i] = l_ii.
-__global__ void k_diag(const float* __restrict__ L, int n, int ld, float* __restrict__ diag) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) diag[i] = L[(size_t)i * ld + i];
-}
-
-// Fixed-order reduction of the row partials into loss, dL/dscale, dL/dbias.
-__global__ __launch_bounds__(256) void k_contrastive_reduce(const float* __restrict__ part,
+// Fixed-order reduction of the workgroups' terms into loss, dL/dscale,
+// dL/dbias.
+__global__ __launch_bounds__(256) void k_contrastive_reduce(const float* __restrict__ part, int np,
                                                             const float* __restrict__ rlse,
                                                             const float* __restrict__ clse,
                                                             const float* __restrict__ diag, int n,
                                                             int head, float scale,
                                                             float* __restrict__ loss,
                                                             float* __restrict__ dsb) {
-  __shared__ float red[3][4];
+  __shared__ float red[4];
   float sl = 0.f, sg = 0.f, s0 = 0.f;
-  for (int i = threadIdx.x; i < n; i += 256) {
-    sl += head == 0 ? (rlse[i] - diag[i]) + (clse[i] - diag[i]) : part[3 * i];
+  if (head == 0)
+    for (int i = threadIdx.x; i < n; i += 256) sl += (rlse[i] - diag[i]) + (clse[i] - diag[i]);
+  for (int i = threadIdx.x; i < np; i += 256) {
+    sl += part[3 * i];
     sg += part[3 * i + 1];
     s0 += part[3 * i + 2];
   }
-  sl = wave_sum(sl); sg = wave_sum(sg); s0 = wave_sum(s0);
-  if ((threadIdx.x & 63) == 0) {
-    red[0][threadIdx.x >> 6] = sl; red[1][threadIdx.x >> 6] = sg; red[2][threadIdx.x >> 6] = s0;
-  }
-  __syncthreads();
+  auto sum = [](float a, float b) { return a + b; };
+  sl = block_reduce(sl, red, sum);
+  sg = block_reduce(sg, red, sum);
+  s0 = block_reduce(s0, red, sum);
   if (threadIdx.x == 0) {
-    const float L = (red[0][0] + red[0][1]) + (red[0][2] + red[0][3]);
-    loss[0] = head == 0 ? 0.5f * L / (float)n : L / (float)n;
-    dsb[0] = ((red[1][0] + red[1][1]) + (red[1][2] + red[1][3])) / scale;
-    dsb[1] = head == 0 ? 0.f : (red[2][0] + red[2][1]) + (red[2][2] + red[2][3]);
+    loss[0] = head == 0 ? 0.5f * sl / (float)n : sl / (float)n;
+    dsb[0] = sg / scale;
+    dsb[1] = head == 0 ? 0.f : s0;
   }
-}
-
-// out [cols_out, ld_out] = in [rows, cols]^T, zero-filled past `rows` up to
-// ld_out columns.  32x32 tiles through LDS.
-__global__ __launch_bounds__(256) void k_transpose_pad(const float* __restrict__ in, int rows,
-                                                       int cols, int ld_in,
-                                                       float* __restrict__ out, int ld_out) {
-  __shared__ float t[32][33];
-  const int r0 = blockIdx.y * 32, c0 = blockIdx.x * 32;
-  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;  // 32 x 8
-  for (int k = ty; k < 32; k += 8) {
-    const int r = r0 + k, c = c0 + tx;
-    t[k][tx] = (r < rows && c < cols) ? in[(size_t)r * ld_in + c] : 0.f;
-  }
-  __syncthreads();
-  for (int k = ty; k < 32; k += 8) {
-    const int c = c0 + k, r = r0 + tx;   // out row c, column r
-    if (c < cols && r < ld_out) out[(size_t)c * ld_out + r] = t[tx][k];
-  }
-}
-
-static hipError_t transpose_pad(const float* in, int rows, int cols, int ld_in, float* out,
-                                int ld_out, hipStream_t s) {
-  dim3 grid((cols + 31) / 32, (ld_out + 31) / 32), block(256);
-  hipLaunchKernelGGL(k_transpose_pad, grid, block, 0, s, in, rows, cols, ld_in, out, ld_out);
-  return hipGetLastError();
 }
 
 size_t contrastive_workspace_bytes(int n, int dim) {
@@ -195,22 +285,32 @@ hipError_t contrastive_loss(const float* E, const float* Tx, int n, int dim, int
   EpiArgs e;
   e.out = L; e.ldo = n16; e.alpha = scale; e.beta = bias;
   if ((err = gemm_f32(E, dim, Tx, dim, n, n, dim, OP_LOGITS, e, s)) != hipSuccess) return err;
-  hipLaunchKernelGGL(k_row_lse, dim3(n), dim3(256), 0, s, L, n, n16, rlse);
-  hipLaunchKernelGGL(k_col_lse, dim3((n + 63) / 64), dim3(256), 0, s, L, n, n16, clse);
-  hipLaunchKernelGGL(k_diag, dim3((n + 255) / 256), dim3(256), 0, s, L, n, n16, diag);
-  hipLaunchKernelGGL(k_contrastive_grad, dim3(n), dim3(256), 0, s, L, n, n16, head, bias, rlse,
-                     clse, part);
-  hipLaunchKernelGGL(k_contrastive_reduce, dim3(1), dim3(256), 0, s, part, rlse, clse, diag, n,
+  const int nt = (n + CT - 1) / CT;
+  // The tiles' row and column parts wait in Gt's place (2 nt n pairs, at most a
+  // quarter of it and 16 n bytes more), which the gradient kernel fills later.
+  float2* rowp = reinterpret_cast<float2*>(Gt);
+  float2* colp = rowp + (size_t)nt * n;
+  const int64_t lse_blocks = (int64_t)nt * nt + 2 * (int64_t)((dim + 31) / 32) * ((n16 + 31) / 32);
+  if (lse_blocks > INT32_MAX) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_lse_parts, dim3((unsigned)lse_blocks), dim3(256), 0, s, L, n, n16, nt, rowp,
+                     colp, E, Tx, dim, Et, Tt);
+  hipLaunchKernelGGL(k_lse_merge, dim3((n + 63) / 64, 2), dim3(256), 0, s, rowp, colp, n, nt, L,
+                     n16, rlse, clse, diag);
+  // One term triple per workgroup, n triples at most (the workspace's share):
+  // one column tile per workgroup up to about 4096 pairs.
+  int per = 1;
+  while ((int64_t)nt * ((nt + per - 1) / per) > n) ++per;
+  const int gb = nt * ((nt + per - 1) / per);
+  hipLaunchKernelGGL(k_contrastive_grad, dim3(gb), dim3(256), 0, s, L, n, n16, nt, per, head, bias,
+                     rlse, clse, Gt, part);
+  hipLaunchKernelGGL(k_contrastive_reduce, dim3(1), dim3(256), 0, s, part, gb, rlse, clse, diag, n,
                      head, scale, loss, dsb);
   if ((err = hipGetLastError()) != hipSuccess) return err;
   // dE = scale * G T : A = G [n, n16], B = T^T [dim, n16]
-  if ((err = transpose_pad(Tx, n, dim, dim, Tt, n16, s)) != hipSuccess) return err;
   EpiArgs ge;
   ge.out = dE; ge.ldo = dim; ge.alpha = scale; ge.beta = 0.f;
   if ((err = gemm_f32(L, n16, Tt, n16, n, dim, n16, OP_LOGITS, ge, s)) != hipSuccess) return err;
   // dT = scale * G^T E : A = G^T [n, n16], B = E^T [dim, n16]
-  if ((err = transpose_pad(L, n, n, n16, Gt, n16, s)) != hipSuccess) return err;
-  if ((err = transpose_pad(E, n, dim, dim, Et, n16, s)) != hipSuccess) return err;
   EpiArgs gt;
   gt.out = dT; gt.ldo = dim; gt.alpha = scale; gt.beta = 0.f;
   return gemm_f32(Gt, n16, Et, n16, n, dim, n16, OP_LOGITS, gt, s);

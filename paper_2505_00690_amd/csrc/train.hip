@@ -704,7 +704,7 @@ constexpr int BWD_ST = 3;    // key / value tile ring stages of the dQ kernel
 // (image, head) share its keys and values in one L2).  LSE_IN: lse2_io holds
 // each query's log-sum-exp (log2 units, from the forward) and is only read;
 // otherwise the same pass over the keys forms and writes it (measured at 32 x
-// 577 tokens, 16 heads of 64: 235 us with a separate pass for it, 158 us so).
+// 577 tokens, 16 heads of 64: 235 us with a separate pass for it, 140 us so).
 // Also writes D = rowsum(dO O) per query and, with dob_out, dO in BF16.
 template <int HD, bool LSE_IN>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k_attn_bwd_dq_mfma(const bf16_t* __restrict__ qkv,
