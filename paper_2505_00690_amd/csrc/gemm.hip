@@ -164,69 +164,111 @@ hipError_t gemm_mx(const uint8_t* A, const uint8_t* SA, const uint8_t* B, const 
   return hipErrorInvalidValue;
 }
 
-// ------------------------------------------------ FP32 GEMM with few A rows
-// The small products of the heads (logits of a few images against many
-// texts, projections of pooled rows): A has few rows and B is the large
-// operand, so 64x64 tiles leave most CUs idle.  A workgroup owns 8 rows of A
-// (staged in LDS in K chunks) and 32 columns; thread (kq, column) sums its
-// column's products with the 8 rows over the float4 chunks kq, kq + 8, kq +
-// 16, ... of K, and the 8 partial sums of an output are added in kq order.
-// Every output is computed the same way whatever M is, so a row's result does
-// not depend on the other rows of the batch.
-constexpr int FR_M = 8, FR_N = 32, FR_KQ = 8, FR_KC = 512;
+// --------------------------------------------- FP32 GEMM of the heads' products
+// The products of the heads (projections of pooled rows, logits of images
+// against texts): one to a few thousand A rows, K of a few hundred.  A
+// workgroup owns 16 RT x 16 RT outputs on v_mfma_f32_16x16x4_f32, whose result
+// is the chain of its four products in k order.  Chain q of an output takes
+// the float4 chunks q, q + 8, q + 16, ... of K, the 8 chains are added in q
+// order, and wave w holds chains w and w + 4.  An output is computed the same
+// way whatever M, N and RT are, so a row's result does not depend on the
+// other rows of the batch.  256 K values of the tile's rows are one stage of
+// LDS, streamed by direct-to-LDS loads of a whole 1 KB row each: RT = 1 keeps
+// 4 stages, RT = 2 two, 133 KB both.  (Operands loaded straight into
+// registers need 16-byte pieces of 16 rows per instruction: scores of 1000 x
+// 1000 over K = 512 took 39 us against 26; the vector-ALU kernel before this
+// one, with the same sums, 58 us.)
+constexpr int FR_KC = 256;                    // K values per stage
+constexpr int FR_LD = FR_KC + 4;              // LDS row: rows 4 banks apart
+constexpr int64_t kRows16Tiles = 256;
 
-template <int OP>
+template <int OP, int RT>
 __global__ __launch_bounds__(256) void k_gemm_f32_rows(const float* __restrict__ A, int lda,
                                                        const float* __restrict__ B, int ldb,
                                                        int M, int N, int K, EpiArgs e) {
   constexpr int EPI = OpEpi<OP>::kind;
-  __shared__ float4 sA[FR_M][FR_KC / 4];
-  __shared__ float sP[FR_KQ][FR_M][FR_N + 1];
-  const int tid = threadIdx.x;
-  const int nl = tid & (FR_N - 1), kq = tid >> 5;
-  const int nbn = (N + FR_N - 1) / FR_N;      // one-dimensional grid: no limit on M
-  const int m0 = (int)(blockIdx.x / nbn) * FR_M, n0 = (int)(blockIdx.x % nbn) * FR_N;
-  const float* brow = B + (size_t)min(n0 + nl, N - 1) * ldb;
-  float acc[FR_M];
+  constexpr int T = 16 * RT, NS = 4 / RT;     // tile side, stages
+  constexpr int LPW = T / 2;                  // rows (loads) per wave and stage
+  __shared__ __attribute__((aligned(16))) float smem[NS * 2 * T * FR_LD];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int nbn = (N + T - 1) / T;            // one-dimensional grid: no limit on M
+  const int m0 = (int)(blockIdx.x / nbn) * T, n0 = (int)(blockIdx.x % nbn) * T;
+  // Rows past M or N repeat the last one; K values past K read as zero (past
+  // the row's buffer).
+  const float* A0 = A + (size_t)m0 * lda;
+  const float* B0 = B + (size_t)n0 * ldb;
+  const int ma = min(T, M - m0) - 1, nb = min(T, N - n0) - 1;
+  const uint32_t lds0 = lds_offset(smem);
+  auto issue = [&](int st, int ch) {
+    const int v = (FR_KC * ch + 4 * lane) * 4;
 #pragma unroll
-  for (int r = 0; r < FR_M; ++r) acc[r] = 0.f;
-  constexpr int NB = FR_KC / 4 / FR_KQ;   // B chunks per thread and K chunk
-  for (int k0 = 0; k0 < K; k0 += FR_KC) {
-    const int nc = min(FR_KC, K - k0) / 4;   // float4 chunks in this K chunk
-    // All of this thread's B loads of the K chunk are issued first, so their
-    // latencies overlap one another and the A staging.
-    float4 b[NB];
-#pragma unroll
-    for (int i = 0; i < NB; ++i) {
-      const int c = kq + FR_KQ * i;
-      b[i] = c < nc ? *reinterpret_cast<const float4*>(brow + k0 + 4 * c)
-                    : make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int j = 0; j < LPW / 2; ++j) {
+      const int row = wave + 4 * j;
+      const uint32_t lo = lds0 + (st * 2 * T + row) * FR_LD * 4;
+      dma16(buffer_rsrc(A0 + (size_t)min(row, ma) * lda, (uint64_t)K * 4), lo, v, 0);
+      dma16(buffer_rsrc(B0 + (size_t)min(row, nb) * ldb, (uint64_t)K * 4), lo + T * FR_LD * 4, v,
+            0);
     }
-    __syncthreads();                          // readers of the previous chunk are done
-    for (int i = tid; i < FR_M * nc; i += 256) {
-      const int r = i / nc, c = i - r * nc;
-      sA[r][c] = *reinterpret_cast<const float4*>(A + (size_t)min(m0 + r, M - 1) * lda + k0 + 4 * c);
+  };
+  f32x4 acc[2][RT][RT];                       // chains w, w + 4
+#pragma unroll
+  for (int h = 0; h < 2; ++h)
+#pragma unroll
+    for (int r = 0; r < RT; ++r)
+#pragma unroll
+      for (int c = 0; c < RT; ++c) acc[h][r][c] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const int nch = (K + FR_KC - 1) / FR_KC;
+  for (int i = 0; i < NS && i < nch; ++i) issue(i, i);
+  const int i = lane & 15, k = lane >> 4;
+  int st = 0;
+  for (int ch = 0; ch < nch; ++ch) {
+    switch (min(NS - 1, nch - 1 - ch)) {      // stages still on their way
+      case 3: asm volatile("s_waitcnt vmcnt(%0)" ::"n"(3 * LPW) : "memory"); break;
+      case 2: asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * LPW) : "memory"); break;
+      case 1: asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LPW) : "memory"); break;
+      default: asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     }
-    __syncthreads();
+    lds_barrier();
+    // Lane (i, k): component k of chunk wave + 4 x of row i.
+    const float* sa = smem + (st * 2 * T + i) * FR_LD + 4 * wave + k;
+    const float* sb = sa + T * FR_LD;
 #pragma unroll
-    for (int i = 0; i < NB; ++i) {
-      const int c = kq + FR_KQ * i;
-      if (c >= nc) break;
+    for (int x = 0; x < FR_KC / 16; ++x) {
+      float a[RT], b[RT];
 #pragma unroll
-      for (int r = 0; r < FR_M; ++r) {
-        const float4 a = sA[r][c];
-        acc[r] = fmaf(a.x, b[i].x, acc[r]);
-        acc[r] = fmaf(a.y, b[i].y, acc[r]);
-        acc[r] = fmaf(a.z, b[i].z, acc[r]);
-        acc[r] = fmaf(a.w, b[i].w, acc[r]);
+      for (int r = 0; r < RT; ++r) {
+        a[r] = sa[r * 16 * FR_LD + 16 * x];
+        b[r] = sb[r * 16 * FR_LD + 16 * x];
       }
-    }
-  }
 #pragma unroll
-  for (int r = 0; r < FR_M; ++r) sP[kq][r][nl] = acc[r];
+      for (int r = 0; r < RT; ++r)
+#pragma unroll
+        for (int c = 0; c < RT; ++c)
+          acc[x & 1][r][c] =
+              __builtin_amdgcn_mfma_f32_16x16x4f32(a[r], b[c], acc[x & 1][r][c], 0, 0, 0);
+    }
+    if (ch + NS < nch) {
+      lds_barrier();                          // every wave has read the stage
+      issue(st, ch + NS);
+    }
+    st = st + 1 == NS ? 0 : st + 1;
+  }
+  lds_barrier();
+  // C layout: lane (column i, k), register q: row 4 k + q.
+  float (*sP)[T][T + 1] = reinterpret_cast<float(*)[T][T + 1]>(smem);
+#pragma unroll
+  for (int h = 0; h < 2; ++h)
+#pragma unroll
+    for (int r = 0; r < RT; ++r)
+#pragma unroll
+      for (int c = 0; c < RT; ++c)
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          sP[wave + 4 * h][16 * r + 4 * k + q][16 * c + i] = acc[h][r][c][q];
   __syncthreads();
-  if (tid >= FR_M * FR_N / 4) return;
-  const int r = tid / (FR_N / 4), nq = (tid % (FR_N / 4)) * 4;
+  if (tid >= T * T / 4) return;
+  const int r = tid / (T / 4), nq = (tid % (T / 4)) * 4;
   const int m = m0 + r, n = n0 + nq;
   if (m >= M || n >= N) return;
   float v[4];
@@ -234,7 +276,7 @@ __global__ __launch_bounds__(256) void k_gemm_f32_rows(const float* __restrict__
   for (int j = 0; j < 4; ++j) {
     float t = sP[0][r][nq + j];
 #pragma unroll
-    for (int q = 1; q < FR_KQ; ++q) t += sP[q][r][nq + j];
+    for (int q = 1; q < 8; ++q) t += sP[q][r][nq + j];
     v[j] = t;
   }
   epi_store4<EPI, false>(e, m, n, v[0], v[1], v[2], v[3]);
@@ -243,12 +285,19 @@ __global__ __launch_bounds__(256) void k_gemm_f32_rows(const float* __restrict__
 hipError_t gemm_f32_rows(const float* A, int lda, const float* B, int ldb, int M, int N, int K,
                          int op, const EpiArgs& e, hipStream_t s) {
   if (M <= 0) return hipSuccess;
-  const int64_t blocks = (int64_t)((N + FR_N - 1) / FR_N) * ((M + FR_M - 1) / FR_M);
+  auto tiles = [&](int t) { return (int64_t)((N + t - 1) / t) * ((M + t - 1) / t); };
+  const bool small = tiles(16) <= kRows16Tiles;
+  const int64_t blocks = tiles(small ? 16 : 32);
   if (blocks > INT32_MAX) return hipErrorInvalidValue;
   dim3 grid((unsigned)blocks), block(256);
-#define VL_GEMM_CASE(OP)                                                                   \
-  case OP:                                                                                 \
-    hipLaunchKernelGGL(k_gemm_f32_rows<OP>, grid, block, 0, s, A, lda, B, ldb, M, N, K, e); \
+#define VL_GEMM_CASE(OP)                                                                      \
+  case OP:                                                                                    \
+    if (small)                                                                                \
+      hipLaunchKernelGGL((k_gemm_f32_rows<OP, 1>), grid, block, 0, s, A, lda, B, ldb, M, N, K, \
+                         e);                                                                  \
+    else                                                                                      \
+      hipLaunchKernelGGL((k_gemm_f32_rows<OP, 2>), grid, block, 0, s, A, lda, B, ldb, M, N, K, \
+                         e);                                                                  \
     break;
   switch (op) {
     VL_GEMM_CASE(OP_QKV)

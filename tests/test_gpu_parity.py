@@ -297,6 +297,35 @@ def test_score_heads(V, head, scale, bias, m, dim):
     assert gtop[3] == 5
 
 
+@pytest.mark.parametrize("dim", [4, 252, 260, 1028, 1100])
+def test_logit_tiles_keep_bits(V, dim):
+    """The head products' tile sizes (16 x 16 up to 256 tiles, 32 x 32 past
+    that) at ragged rows, columns and K, on either side of the K stages: each
+    score against FP64, and a row's bits whatever batch it is in."""
+    rng = np.random.Generator(np.random.PCG64(dim))
+    e = rng.standard_normal((103, dim))
+    e = (e / np.linalg.norm(e, axis=1, keepdims=True)).astype(np.float32)
+    t = synth.make_texts(620, dim, 3100)
+    ed, td = torch.from_numpy(e).cuda(), torch.from_numpy(t).cuda()
+
+    def score(rows, texts):
+        sc = torch.empty((rows.shape[0], texts.shape[0]), dtype=torch.float32, device="cuda")
+        V.vl_score(rows, texts, "sigmoid", 10.0, -1.0, sc,
+                   torch.empty(rows.shape[0], dtype=torch.int32, device="cuda"))
+        torch.cuda.synchronize()
+        return sc
+
+    big = score(ed, td)               # 7 x 39 tiles of 16, 4 x 20 of 32
+    p_ref, _ = O.score(e, t, "sigmoid", 10.0, -1.0)
+    # |d p| <= |d logit| / 4; a logit is 8 chains of at most dim / 8 rounded
+    # products of unit vectors, their sum, the scale and the bias.
+    tol = ((dim / 8 + 12) * 10 + 11) * 2.0 ** -24 / 4 + 4 * 2.0 ** -24
+    assert float(np.max(np.abs(big.cpu().numpy() - p_ref))) <= tol
+    assert torch.equal(score(ed[:1], td), big[:1])
+    assert torch.equal(score(ed[16:49], td[:132]), big[16:49, :132])
+    assert torch.equal(score(ed[102:], td[616:]), big[102:, 616:])
+
+
 # ------------------------------------------------- full-size configurations
 # Every image of every full-size batch against the FP64 oracle embeddings
 # that tests/golden/make_goldens.py wrote (it calls only oracle/ and synth/).
