@@ -235,7 +235,7 @@ __global__ __launch_bounds__(256) void k_attn_bf16(const bf16_t* __restrict__ qk
       asm("v_max3_f32 %0, %1, %2, %3" : "=v"(mt) : "v"(mt), "v"(x), "v"(y));
     }
     asm("v_max_f32 %0, %1, %2" : "=v"(mt) : "v"(mt), "v"(s[1][15]));
-    mt = fmaxf(mt, __shfl_xor(mt, 32, 64)) * sl2;
+    mt = xor_op<32>(mt, MaxOp()) * sl2;
     if (__any(mt > m_run + ATT_TAU)) {
       const float m_new = fmaxf(m_run, mt);
       const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
@@ -281,7 +281,7 @@ __global__ __launch_bounds__(256) void k_attn_bf16(const bf16_t* __restrict__ qk
     if (kt + 2 < KT) tile(std::integral_constant<int, 2>(), kt + 2);
   }
   if (!wave_active || q >= N) return;
-  const float lt = l_run + __shfl_xor(l_run, 32, 64);
+  const float lt = xor_op<32>(l_run, AddOp());
   const float inv = 1.f / lt;
   if (lse_out && g == 0) lse_out[(size_t)(dsc.tok_start + q) * heads + h] = m_run + log2f(lt);
   if constexpr (MX) {
@@ -293,7 +293,7 @@ __global__ __launch_bounds__(256) void k_attn_bf16(const bf16_t* __restrict__ qk
       float am = 0.f;
 #pragma unroll
       for (int r = 0; r < 16; ++r) am = fmaxf(am, fabsf(o[a][r]));
-      am = fmaxf(am, __shfl_xor(am, 32, 64)) * inv;
+      am = xor_op<32>(am, MaxOp()) * inv;
       const uint32_t sb = mx_scale_byte(am);
       const float si = mx_inv_scale(sb);
 #pragma unroll
@@ -446,7 +446,7 @@ __global__ __launch_bounds__(RES_W * 64) void k_attn_bf16_res(
       asm("v_max3_f32 %0, %1, %2, %3" : "=v"(mt) : "v"(mt), "v"(x), "v"(y));
     }
     asm("v_max_f32 %0, %1, %2" : "=v"(mt) : "v"(mt), "v"(s[1][15]));
-    mt = fmaxf(mt, __shfl_xor(mt, 32, 64)) * sl2;
+    mt = xor_op<32>(mt, MaxOp()) * sl2;
     if (__any(mt > m_run + ATT_TAU)) {
       const float m_new = fmaxf(m_run, mt);
       const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
@@ -482,7 +482,7 @@ __global__ __launch_bounds__(RES_W * 64) void k_attn_bf16_res(
     }
   };
   auto store = [&](const f32x16* o, float m_run, float l_run, int q) {
-    const float lt = l_run + __shfl_xor(l_run, 32, 64);
+    const float lt = xor_op<32>(l_run, AddOp());
     if (q >= N) return;
     const float inv = 1.f / lt;
     if (lse_out && g == 0) lse_out[(size_t)(dsc.tok_start + q) * heads + h] = m_run + log2f(lt);
@@ -494,7 +494,7 @@ __global__ __launch_bounds__(RES_W * 64) void k_attn_bf16_res(
         float am = 0.f;
 #pragma unroll
         for (int r = 0; r < 16; ++r) am = fmaxf(am, fabsf(o[a][r]));
-        am = fmaxf(am, __shfl_xor(am, 32, 64)) * inv;
+        am = xor_op<32>(am, MaxOp()) * inv;
         const uint32_t sb = mx_scale_byte(am);
         const float si = mx_inv_scale(sb);
 #pragma unroll
@@ -735,7 +735,7 @@ __global__ __launch_bounds__(256) void k_attn_f32(const float* __restrict__ qkv,
       s[r] = k0 + 8 * (r >> 2) + 4 * g + (r & 3) <= kmax ? s[r] * sc : -INFINITY;
       mt = fmaxf(mt, s[r]);
     }
-    mt = fmaxf(mt, __shfl_xor(mt, 32, 64));
+    mt = xor_op<32>(mt, MaxOp());
     // (key 0 is visible to every query, so the maximum is finite from the
     // first tile on)
     const float m_new = fmaxf(m_run, mt);
@@ -762,7 +762,7 @@ __global__ __launch_bounds__(256) void k_attn_f32(const float* __restrict__ qkv,
       }
   }
   if (!wave_active || q >= N) return;
-  const float inv = 1.f / (l_run + __shfl_xor(l_run, 32, 64));
+  const float inv = 1.f / (xor_op<32>(l_run, AddOp()));
   float* op = out + (size_t)(dsc.tok_start + q) * D + h * HD;
 #pragma unroll
   for (int a = 0; a < NA; ++a)

@@ -47,16 +47,51 @@ __device__ __forceinline__ uint32_t e4m3_to_bf16_bits(uint32_t b) {
   return s | r;
 }
 
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
+// op(v, v of lane ^ O) on the vector ALU (lane swaps and DPP).  op is
+// commutative, so both lanes of a pair get the same bits.  The LDS permute
+// that __shfl_xor becomes costs its round trip: a LayerNorm's two sums are
+// twelve of them in a row, a quarter of a small launch.
+template <int O, typename Op>
+__device__ __forceinline__ float xor_op(float v, Op op) {
+  const int x = __builtin_bit_cast(int, v);
+  if constexpr (O == 32 || O == 16) {
+    // v_permlane{32,16}_swap of v with itself: the pair's two values, the
+    // same in both lanes.
+    const auto r = O == 32 ? __builtin_amdgcn_permlane32_swap(x, x, false, false)
+                           : __builtin_amdgcn_permlane16_swap(x, x, false, false);
+    const uint32_t r0 = r[0], r1 = r[1];   // (elements: no bit_cast of them)
+    return op(__builtin_bit_cast(float, r0), __builtin_bit_cast(float, r1));
+  } else {
+    int y;
+    if constexpr (O == 8) {                 // row_ror:8
+      y = __builtin_amdgcn_update_dpp(x, x, 0x128, 0xf, 0xf, false);
+    } else if constexpr (O == 4) {          // row_shl:4 in the even quads, row_shr:4 in the odd
+      y = __builtin_amdgcn_update_dpp(x, x, 0x104, 0xf, 0x5, false);
+      y = __builtin_amdgcn_update_dpp(y, x, 0x114, 0xf, 0xa, false);
+    } else {                                // quad_perm
+      static_assert(O == 2 || O == 1);
+      y = __builtin_amdgcn_update_dpp(x, x, O == 2 ? 0x4e : 0xb1, 0xf, 0xf, false);
+    }
+    return op(v, __builtin_bit_cast(float, y));
+  }
 }
-__device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
-  return v;
+struct AddOp {
+  __device__ __forceinline__ float operator()(float a, float b) const { return a + b; }
+};
+struct MaxOp {
+  __device__ __forceinline__ float operator()(float a, float b) const { return fmaxf(a, b); }
+};
+template <typename Op>
+__device__ __forceinline__ float wave_reduce(float v, Op op) {
+  v = xor_op<32>(v, op);
+  v = xor_op<16>(v, op);
+  v = xor_op<8>(v, op);
+  v = xor_op<4>(v, op);
+  v = xor_op<2>(v, op);
+  return xor_op<1>(v, op);
 }
+__device__ __forceinline__ float wave_sum(float v) { return wave_reduce(v, AddOp()); }
+__device__ __forceinline__ float wave_max(float v) { return wave_reduce(v, MaxOp()); }
 
 // GELU(x) = x * Phi(x) = x/2 * (1 + erf(x / sqrt 2)), exact-erf form.
 __device__ __forceinline__ float gelu_erf(float x) {
@@ -202,8 +237,7 @@ __device__ __forceinline__ i32x4 buffer_rsrc(const void* base, uint64_t bytes) {
 template <typename Op>
 __device__ __forceinline__ float block_reduce(float v, float* red, Op op) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = op(v, __shfl_xor(v, o, 64));
+  v = wave_reduce(v, op);
   __syncthreads();
   if (lane == 0) red[w] = v;
   __syncthreads();

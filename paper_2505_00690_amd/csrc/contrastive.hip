@@ -28,15 +28,15 @@ __device__ __forceinline__ float2 lse_part(const float (&v)[16]) {
   float mx = v[0];
 #pragma unroll
   for (int j = 1; j < 16; ++j) mx = fmaxf(mx, v[j]);
-  mx = fmaxf(mx, __shfl_xor(mx, 1, 64));
-  mx = fmaxf(mx, __shfl_xor(mx, 2, 64));
+  mx = xor_op<1>(mx, MaxOp());
+  mx = xor_op<2>(mx, MaxOp());
   float s = 0.f;
   if (mx > -INFINITY) {   // else no value in range (or none above -inf)
 #pragma unroll
     for (int j = 0; j < 16; ++j) s += expf(v[j] - mx);
   }
-  s += __shfl_xor(s, 1, 64);
-  s += __shfl_xor(s, 2, 64);
+  s = xor_op<1>(s, AddOp());
+  s = xor_op<2>(s, AddOp());
   return make_float2(mx, s);
 }
 

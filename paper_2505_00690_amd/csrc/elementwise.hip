@@ -139,9 +139,9 @@ __global__ __launch_bounds__(256) void k_ln_stats(const float* __restrict__ part
   const float2* pr = reinterpret_cast<const float2*>(parts) + min(row, M - 1);
   float sm = 0.f;
   for (int g = j; g < G; g += 8) sm += pr[(size_t)g * M].x;
-  sm += __shfl_xor(sm, 1, 64);
-  sm += __shfl_xor(sm, 2, 64);
-  sm += __shfl_xor(sm, 4, 64);
+  sm = xor_op<1>(sm, AddOp());
+  sm = xor_op<2>(sm, AddOp());
+  sm = xor_op<4>(sm, AddOp());
   const float mean = sm / (float)G;
   float t = 0.f;
   for (int g = j; g < G; g += 8) {
@@ -149,9 +149,9 @@ __global__ __launch_bounds__(256) void k_ln_stats(const float* __restrict__ part
     const float d = v.x - mean;
     t += fmaf(32.f, d * d, v.y);
   }
-  t += __shfl_xor(t, 1, 64);
-  t += __shfl_xor(t, 2, 64);
-  t += __shfl_xor(t, 4, 64);
+  t = xor_op<1>(t, AddOp());
+  t = xor_op<2>(t, AddOp());
+  t = xor_op<4>(t, AddOp());
   if (row < M && j == 0)
     *reinterpret_cast<float2*>(st + 2 * (size_t)row) =
         make_float2(mean, rsqrtf(t / (float)(32 * G) + eps));

@@ -911,15 +911,15 @@ __attribute__((amdgpu_waves_per_eu(LOOP == LOOP_SMALL ? 2 : WGM * WGN / 4,
             pk.y = pack_bf16x2(xn.z * g4.z, xn.w * g4.w);
             *reinterpret_cast<u32x2*>(e.u_out + (size_t)m * e.ldo + n) = pk;
             float sm = (xn.x + xn.y) + (xn.z + xn.w);
-            sm += __shfl_xor(sm, 1, 64);
-            sm += __shfl_xor(sm, 2, 64);
-            sm += __shfl_xor(sm, 4, 64);
+            sm = xor_op<1>(sm, AddOp());
+            sm = xor_op<2>(sm, AddOp());
+            sm = xor_op<4>(sm, AddOp());
             const float mg = sm * (1.f / 32.f);
             const float d0 = xn.x - mg, d1 = xn.y - mg, d2 = xn.z - mg, d3 = xn.w - mg;
             float q = (d0 * d0 + d1 * d1) + (d2 * d2 + d3 * d3);
-            q += __shfl_xor(q, 1, 64);
-            q += __shfl_xor(q, 2, 64);
-            q += __shfl_xor(q, 4, 64);
+            q = xor_op<1>(q, AddOp());
+            q = xor_op<2>(q, AddOp());
+            q = xor_op<4>(q, AddOp());
             if ((rc & 7) == 0)   // group-major: consecutive rows are adjacent
               *reinterpret_cast<float2*>(e.part_stats + ((size_t)(n >> 5) * M + m) * 2) =
                   make_float2(mg, q);

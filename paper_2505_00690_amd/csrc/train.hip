@@ -455,8 +455,8 @@ __global__ __launch_bounds__(256) void k_attn_bwd_dq(const T* __restrict__ qkv,
   float dsv = 0.f;
 #pragma unroll
   for (int k = 0; k < KQ; ++k) dsv += sdO[r][cq * KQ + k] * sV[r][cq * KQ + k];
-  dsv += __shfl_xor(dsv, 1);
-  dsv += __shfl_xor(dsv, 2);
+  dsv = xor_op<1>(dsv, AddOp());
+  dsv = xor_op<2>(dsv, AddOp());
   __syncthreads();
   auto load_kv = [&](int k0, int nk, bool with_v) {
     for (int i = tid; i < AB * HD; i += 256) {
@@ -483,14 +483,14 @@ __global__ __launch_bounds__(256) void k_attn_bwd_dq(const T* __restrict__ qkv,
       sc[j] = c < nk ? a * scale : -INFINITY;
       tmax = fmaxf(tmax, sc[j]);
     }
-    tmax = fmaxf(tmax, __shfl_xor(tmax, 1));
-    tmax = fmaxf(tmax, __shfl_xor(tmax, 2));
+    tmax = xor_op<1>(tmax, MaxOp());
+    tmax = xor_op<2>(tmax, MaxOp());
     const float mnew = fmaxf(mrow, tmax);
     float ts = 0.f;
 #pragma unroll
     for (int j = 0; j < 16; ++j) ts += expf(sc[j] - mnew);
-    ts += __shfl_xor(ts, 1);
-    ts += __shfl_xor(ts, 2);
+    ts = xor_op<1>(ts, AddOp());
+    ts = xor_op<2>(ts, AddOp());
     lrow = lrow * expf(mrow - mnew) + ts;
     mrow = mnew;
     __syncthreads();
@@ -754,7 +754,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
 #pragma unroll
     for (int e = 0; e < 8; ++e) dsv += xs[e] * bf16_bits_to_f32(op[e]);
   }
-  dsv += __shfl_xor(dsv, 32, 64);
+  dsv = xor_op<32>(dsv, AddOp());
   const float sl2 = 1.4426950408889634f / sqrtf((float)HD);
   if (dob_out && qok) {   // this head's columns of dO in BF16, for the dK/dV kernel
 #pragma unroll
@@ -846,7 +846,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
           const int key = k0 + 32 * kb + 8 * (r >> 2) + 4 * g + (r & 3);
           mt = fmaxf(mt, key < N ? s[r] : -INFINITY);
         }
-        mt = fmaxf(mt, __shfl_xor(mt, 32, 64)) * sl2;
+        mt = xor_op<32>(mt, MaxOp()) * sl2;
         if (__any(mt > ref + 8.f)) {
           const float m_new = fmaxf(ref, mt);
           const float alpha = __builtin_amdgcn_exp2f(ref - m_new);
@@ -888,7 +888,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
   if (!qok) return;
   float scale = 1.0f / sqrtf((float)HD);
   if (!LSE_IN) {
-    lsum += __shfl_xor(lsum, 32, 64);
+    lsum = xor_op<32>(lsum, AddOp());
     scale /= lsum;
   }
   const size_t row = (size_t)dsc.tok_start + q;
