@@ -839,13 +839,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
         const bf16x8 vf = *reinterpret_cast<const bf16x8*>(tV + voff[kb][c]);
         dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, df[c], dp, 0, 0, 0);
       }
+      // Keys past the image (zero rows, score 0): p = exp2(-inf) = 0.
+      if (k0 + 32 * kb + 32 > N) {
+  #pragma unroll
+        for (int r = 0; r < 16; ++r)
+          if (k0 + 32 * kb + 8 * (r >> 2) + 4 * g + (r & 3) >= N) s[r] = -INFINITY;
+      }
       if constexpr (!LSE_IN) {
-        float mt = -INFINITY;
+        float mt = s[0];
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int key = k0 + 32 * kb + 8 * (r >> 2) + 4 * g + (r & 3);
-          mt = fmaxf(mt, key < N ? s[r] : -INFINITY);
-        }
+        for (int r = 1; r < 16; ++r) mt = fmaxf(mt, s[r]);
         mt = xor_op<32>(mt, MaxOp()) * sl2;
         if (__any(mt > ref + 8.f)) {
           const float m_new = fmaxf(ref, mt);
@@ -860,10 +863,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
       }
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        const int key = k0 + 32 * kb + 8 * (r >> 2) + 4 * g + (r & 3);
-        // (a key past the image has a zero row, score 0; its p could
-        // overflow for a very negative reference, so it is selected away)
-        const float p = key < N ? __builtin_amdgcn_exp2f(fmaf(s[r], sl2, -ref)) : 0.f;
+        const float p = __builtin_amdgcn_exp2f(fmaf(s[r], sl2, -ref));
         if (!LSE_IN) lsum += p;
         s[r] = p * (dp[r] - dsv);
       }
