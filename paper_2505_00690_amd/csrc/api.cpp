@@ -212,6 +212,8 @@ PlanModel plan_model(const vl_model* m) {
   PlanModel pm;
   pm.text = m->text;
   pm.split = m->split && m->prec != VL_FP32;
+  pm.heads = m->heads;
+  pm.res_rule = true;
   pm.resident = m->attn_resident && m->prec != VL_FP32 && m->hd == 64 && !m->text;
   pm.map_pool = !m->text && m->cfg.pool == VL_POOL_MAP;
   pm.fold_buffers = m->prec == VL_BF16 || m->prec == VL_FP8W_BF16A;
@@ -1462,7 +1464,7 @@ struct AttnPlan {
   int64_t T = 0;
 };
 
-bool attention_plan(int32_t n, const int32_t* lens, bool resident, AttnPlan* ap,
+bool attention_plan(int32_t n, const int32_t* lens, int heads, bool resident, AttnPlan* ap,
                     std::string* why) {
   if (n <= 0 || n > kMaxItems) { *why = "n_seqs must be 1..65535"; return false; }
   if (!lens) { *why = "lengths is NULL"; return false; }
@@ -1470,6 +1472,9 @@ bool attention_plan(int32_t n, const int32_t* lens, bool resident, AttnPlan* ap,
   std::vector<AttnItem> items;
   std::vector<int32_t> res;
   int64_t t = 0;
+  resident = resident && n <= 256 && resident_pays(n, heads, [&](int i) {
+    return std::min<int>(lens[i], kMaxAttnLen);
+  });
   for (int i = 0; i < n; ++i) {
     if (lens[i] < 1 || lens[i] > kMaxAttnLen) {
       *why = "sequence " + std::to_string(i) + " has length " + std::to_string(lens[i]) +
@@ -1491,6 +1496,8 @@ bool attention_plan(int32_t n, const int32_t* lens, bool resident, AttnPlan* ap,
   }
   if (t > (1LL << 24)) { *why = "more than 2^24 tokens"; return false; }
   auto a16 = [](size_t x) { return (x + 15) / 16 * 16; };
+  order_attention(&items, seqs.data(), heads);
+  order_attention(&res, seqs.data(), heads);
   ap->off_items = a16(sizeof(ImgDesc) * n);
   ap->off_res = a16(ap->off_items + sizeof(AttnItem) * items.size());
   ap->desc.assign(ap->off_res + sizeof(int32_t) * res.size(), 0);
@@ -1538,6 +1545,8 @@ bool attention_bwd_plan(int32_t n, const int32_t* lens, int heads, int head_dim,
   }
   if (t > (1LL << 24)) { *why = "more than 2^24 tokens"; return false; }
   auto a16 = [](size_t x) { return (x + 15) / 16 * 16; };
+  order_attention(&it64, seqs.data(), heads);
+  order_attention(&it128, seqs.data(), heads);
   bp->off_items64 = a16(sizeof(ImgDesc) * n);
   bp->off_items128 = a16(bp->off_items64 + sizeof(AttnItem) * it64.size());
   bp->desc.assign(bp->off_items128 + sizeof(AttnItem) * it128.size(), 0);
@@ -1562,7 +1571,7 @@ extern "C" {
 size_t vl_attention_workspace_bytes(int32_t n_seqs, const int32_t* lengths) {
   AttnPlan ap;
   std::string why;
-  if (!attention_plan(n_seqs, lengths, false, &ap, &why)) return 0;
+  if (!attention_plan(n_seqs, lengths, 8, false, &ap, &why)) return 0;
   // an upper bound for every precision: all work items plus a resident list
   return align_up(ap.desc.size() + sizeof(int32_t) * (size_t)n_seqs + 16);
 }
@@ -1581,7 +1590,7 @@ vl_status vl_attention(const void* qkv, vl_precision prec, const int32_t* length
   AttnPlan ap;
   std::string why;
   const bool resident = prec == VL_BF16 && head_dim == 64 && causal == 0;
-  if (!attention_plan(n_seqs, lengths, resident, &ap, &why)) return fail(VL_ERR_INVALID_ARG, why);
+  if (!attention_plan(n_seqs, lengths, heads, resident, &ap, &why)) return fail(VL_ERR_INVALID_ARG, why);
   const std::vector<char>& desc = ap.desc;
   if (ws_bytes < align_up(desc.size()))
     return fail(VL_ERR_WORKSPACE_TOO_SMALL, "workspace too small");

@@ -22,6 +22,33 @@ int cap_images(int n) {
 
 namespace {
 
+template <typename E, typename F>
+void order_entries(std::vector<E>* v, int heads, F ntok) {
+  bool same = true;
+  for (const E& e : *v) same = same && ntok(e) == ntok(v->front());
+  if (same) return;
+  std::stable_sort(v->begin(), v->end(),
+                   [&](const E& a, const E& b) { return ntok(a) > ntok(b); });
+  const size_t runs = heads % 8 == 0 ? 1 : heads % 4 == 0 ? 2 : heads % 2 == 0 ? 4 : 8;
+  if (runs == 1) return;
+  std::vector<E> o;
+  o.reserve(v->size());
+  for (size_t r = 0; r < runs; ++r)
+    for (size_t i = r; i < v->size(); i += runs) o.push_back((*v)[i]);
+  v->swap(o);
+}
+
+}  // namespace
+
+void order_attention(std::vector<AttnItem>* items, const ImgDesc* imgs, int heads) {
+  order_entries(items, heads, [&](const AttnItem& it) { return imgs[it.img].ntok; });
+}
+void order_attention(std::vector<int32_t>* resident, const ImgDesc* imgs, int heads) {
+  order_entries(resident, heads, [&](int32_t i) { return imgs[i].ntok; });
+}
+
+namespace {
+
 // The common tail of planning: part boundaries, attention work items, the
 // descriptor blob and the workspace regions.  imgs[] hold absolute token
 // starts on entry.
@@ -45,13 +72,16 @@ bool finish_plan(const PlanModel& m, std::vector<ImgDesc>& imgs, int64_t T, Plan
   p->parts.clear();
   std::vector<std::vector<AttnItem>> items(cut.size() - 1);
   std::vector<std::vector<int32_t>> res(cut.size() - 1);
-  const bool res_ok = m.resident && !m.text;
   size_t doff = 0;
   for (size_t k = 0; k + 1 < cut.size(); ++k) {
     Part q;
     q.i0 = cut[k];
     q.n = cut[k + 1] - cut[k];
     const int t0 = imgs[q.i0].tok_start;
+    bool res_ok = m.resident && !m.text;
+    if (res_ok && m.res_rule)
+      res_ok = !bucketed &&
+               resident_pays(q.n, m.heads, [&](int i) { return imgs[q.i0 + i].ntok; });
     for (int i = q.i0; i < cut[k + 1]; ++i) {
       imgs[i].tok_start -= t0;
       q.T += imgs[i].ntok;
@@ -64,6 +94,8 @@ bool finish_plan(const PlanModel& m, std::vector<ImgDesc>& imgs, int64_t T, Plan
         for (int q0 = 0; q0 < nt; q0 += kAttnQ) items[k].push_back(AttnItem{i - q.i0, q0});
       }
     }
+    order_attention(&items[k], imgs.data() + q.i0, m.heads);
+    order_attention(&res[k], imgs.data() + q.i0, m.heads);
     q.n_items = (int)items[k].size();
     q.n_res = (int)res[k].size();
     q.T_cap = q.T; q.n_cap = q.n; q.items_cap = q.n_items; q.res_cap = q.n_res;

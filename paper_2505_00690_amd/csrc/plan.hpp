@@ -26,6 +26,38 @@ constexpr int kMaxItems = 65535;   // images / texts per call (grid y of the gat
 constexpr int64_t kSplitMinTokens = 4096;  // two-part batches from this many tokens
 constexpr int64_t kMaxBatchTokens = int64_t(1) << 24;
 
+// Orders attention work (items of sequences imgs[], or a resident list of
+// their indices) longest sequence first, so that the last workgroups to start
+// are short ones.  The kernels give each XCD a contiguous range of the (head,
+// entry) pairs; where `heads` is no multiple of the 8 XCDs these cut a head's
+// entries, so the order is then dealt round-robin into runs of equal total
+// length, one after the other.  Sequences of one length keep their order.
+// (Resident kernel on 100 sequences of 1 .. 640 tokens, 16 heads: 133 us in
+// batch order, 110 so; streaming kernel on 30 of 1 .. 1500, head width 32: 114,
+// 108.)
+void order_attention(std::vector<AttnItem>* items, const ImgDesc* imgs, int heads);
+void order_attention(std::vector<int32_t>* resident, const ImgDesc* imgs, int heads);
+
+// Whether K/V-resident attention is the faster form for a batch or part of n
+// sequences (token counts ntok(i)).  Both forms give the same bits.  A
+// resident workgroup has a CU to itself (160 KB of LDS, two waves per SIMD);
+// the streaming kernel keeps three waves per SIMD, spreads a sequence over
+// ceil(ntok / 128) workgroups and lets ragged lengths even out, and reads keys
+// and values from L2 more often.  That is the better use of the chip (16
+// heads, us, resident / streamed: one image of 577 tokens 35 / 17, 12 images
+// 37.4 / 35.0, 32 of 512 59 / 56, 48 of 577 110 / 107; 12 heads: 96 of 197
+// 52 / 42, 48 of 442 71 / 54; 100 of 1 .. 640 110 / 99) except when the
+// (image, head) pairs are just one per CU and the key tiles many and equal: 16
+// of 577 39.4 / 40.8, 14 38.7 / 39.6, 16 of 512 30.8 / 32.1, of 442 28.4 /
+// 28.8, of 320 21.9 / 20.5.
+template <typename F>
+bool resident_pays(int n, int heads, F ntok) {
+  const int tiles = (ntok(0) + 63) / 64;
+  for (int i = 0; i < n; ++i)
+    if ((ntok(i) + 63) / 64 != tiles) return false;
+  return tiles >= 7 && tiles <= kResMaxTiles && n * heads <= 256 && n * heads >= 224;
+}
+
 // What planning needs to know of a model.
 struct PlanModel {
   bool text = false;          // sequences of token ids (else images)
@@ -38,6 +70,9 @@ struct PlanModel {
   int D = 0, F = 0, Kpad = 0, Pd = 0;  // width, MLP width, padded patch length, output dim
   int P = 1, channels = 3;    // patch side and input planes (images)
   int ctx = 0;                // longest sequence (texts)
+  int heads = 8;              // attention heads
+  bool res_rule = false;      // resident only where resident_pays(), and not in bucketed
+                              // plans, whose batches differ; else every sequence that fits
 };
 
 // A batch runs as one or two parts.  A part is a run of consecutive images

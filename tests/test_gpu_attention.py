@@ -246,3 +246,16 @@ def test_fp32_tile_edges(V, d, causal):
     ref, mag, _, _ = oracle_attention(x, lengths, heads, d, causal)
     got = _run(V, x, lengths, heads, d, causal, "fp32")
     assert np.all(np.abs(got - ref) <= 1e-4 * mag)
+
+
+@pytest.mark.parametrize("n,heads,length", [(14, 16, 577), (16, 16, 640), (60, 4, 385),
+                                            (21, 12, 448)])
+def test_resident_rule_keeps_bits(V, n, heads, length):
+    """One (image, head) pair per CU and equal lengths run K/V-resident; with
+    one more, short sequence the batch streams.  Same bits, on logits that
+    reach the rescale."""
+    rng = np.random.Generator(np.random.PCG64(31 + length))
+    x = _bf16_round(_qkv([length] * n + [3], heads, 64, rng, qk_std=math.sqrt(10.0)))
+    a = _run(V, x[:n * length], [length] * n, heads, 64, False, "bf16")
+    b = _run(V, x, [length] * n + [3], heads, 64, False, "bf16")
+    assert np.array_equal(a, b[:n * length])

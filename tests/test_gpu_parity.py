@@ -722,6 +722,26 @@ def test_resident_attention_bitwise_equal_streaming(V, precision):
     enc.close()
 
 
+@pytest.mark.parametrize("precision,n", [("bf16", 18), ("bf16", 19), ("bf16", 21),
+                                         ("mxfp8", 21), ("bf16", 22)])
+def test_resident_rule_bitwise_equal_streaming(V, precision, n):
+    """Around the batches that run K/V-resident (equal images of at least 7
+    key tiles, 224 .. 256 (image, head) pairs: here 19 .. 21 images of 442
+    tokens, 12 heads): the bits of the streamed batch."""
+    sizes = [(336, 336)] * n
+    imgs = synth.make_images(sizes, 2850)
+    pix = torch.from_numpy(pack(imgs)).cuda()
+    w = torch.from_numpy(blob("b16", 1001)).cuda()
+    enc = V.Encoder(synth.MODELS["b16"], w, precision)
+    V.vl_model_set_option(enc.handle, V.VL_OPT_SPLIT, 0)
+    a = enc.encode(pix, sizes).clone()
+    V.vl_model_set_option(enc.handle, V.VL_OPT_ATTN_RESIDENT, 0)
+    b = enc.encode(pix, sizes).clone()
+    torch.cuda.synchronize()
+    assert torch.equal(a, b)
+    enc.close()
+
+
 # ---------------------------------------------------- LayerNorm folding
 @pytest.mark.parametrize("model,seed,precision,sizes", [
     ("b16", 1001, "bf16", [(224, 224)] * 3 + [(336, 336), (448, 448)]),
