@@ -214,6 +214,7 @@ PlanModel plan_model(const vl_model* m) {
   pm.split = m->split && m->prec != VL_FP32;
   pm.heads = m->heads;
   pm.res_rule = true;
+  pm.short_ok = m->prec == VL_BF16 || m->prec == VL_FP8W_BF16A;
   pm.resident = m->attn_resident && m->prec != VL_FP32 && m->hd == 64 && !m->text;
   pm.map_pool = !m->text && m->cfg.pool == VL_POOL_MAP;
   pm.fold_buffers = m->prec == VL_BF16 || m->prec == VL_FP8W_BF16A;
@@ -397,8 +398,11 @@ vl_status run_part(vl_model* m, const Part& p, const void* in, float* emb, char*
                                        gemm_cfg_for(m, 1, T), e1, s)));
       if (after_first_qkv && li == 0) VL_HIP(hipEventRecord(after_first_qkv, s));
       VL_TIMED(T_ATTN, {
-        VL_HIP(attention_bf16(qh, static_cast<bf16_t*>(Y), d_imgs, d_items, p.n_items, m->heads,
-                              m->hd, m->text, s));
+        VL_HIP(attention_bf16(qh, static_cast<bf16_t*>(Y), d_imgs, d_items, p.n_items - p.n_short,
+                              m->heads, m->hd, m->text, s));
+        VL_HIP(attention_bf16_short(qh, static_cast<bf16_t*>(Y), d_imgs,
+                                    d_items + p.n_items - p.n_short, p.n_short, m->heads, m->hd,
+                                    m->text, s));
         VL_HIP(attention_bf16_resident(qh, Y, nullptr, false, T, d_imgs, d_res, p.n_res,
                                        p.res_tiles, m->heads, m->hd, s));
       });
@@ -473,8 +477,11 @@ vl_status run_part(vl_model* m, const Part& p, const void* in, float* emb, char*
                                        gemm_cfg_for(m, 1, T), e1, s)));
       if (after_first_qkv && &ly == &m->layers[0]) VL_HIP(hipEventRecord(after_first_qkv, s));
       VL_TIMED(T_ATTN, {
-        VL_HIP(attention_bf16(qh, static_cast<bf16_t*>(Y), d_imgs, d_items, p.items_cap,
-                              m->heads, m->hd, m->text, s, bc));
+        VL_HIP(attention_bf16(qh, static_cast<bf16_t*>(Y), d_imgs, d_items,
+                              p.items_cap - p.n_short, m->heads, m->hd, m->text, s, bc));
+        VL_HIP(attention_bf16_short(qh, static_cast<bf16_t*>(Y), d_imgs,
+                                    d_items + p.n_items - p.n_short, p.n_short, m->heads, m->hd,
+                                    m->text, s));
         VL_HIP(attention_bf16_resident(qh, Y, nullptr, false, T, d_imgs, d_res, p.res_cap,
                                        p.res_class, m->heads, m->hd, s, bc));
       });
@@ -1460,53 +1467,65 @@ constexpr int kMaxAttnLen = 4096;  // longest sequence vl_attention accepts
 struct AttnPlan {
   std::vector<char> desc;
   size_t off_items = 0, off_res = 0;
-  int n_items = 0, n_res = 0, res_tiles = 0;
+  int n_items = 0, n_short = 0, n_res = 0, res_tiles = 0;
   int64_t T = 0;
 };
 
-bool attention_plan(int32_t n, const int32_t* lens, int heads, bool resident, AttnPlan* ap,
-                    std::string* why) {
+// Checks a call's lengths; their sum, and the number of `step`-token blocks.
+bool attention_lengths(int32_t n, const int32_t* lens, int step, int64_t* T, size_t* blocks,
+                       std::string* why) {
   if (n <= 0 || n > kMaxItems) { *why = "n_seqs must be 1..65535"; return false; }
   if (!lens) { *why = "lengths is NULL"; return false; }
-  std::vector<ImgDesc> seqs(n);
-  std::vector<AttnItem> items;
-  std::vector<int32_t> res;
-  int64_t t = 0;
-  resident = resident && n <= 256 && resident_pays(n, heads, [&](int i) {
-    return std::min<int>(lens[i], kMaxAttnLen);
-  });
+  *T = 0;
+  *blocks = 0;
   for (int i = 0; i < n; ++i) {
     if (lens[i] < 1 || lens[i] > kMaxAttnLen) {
       *why = "sequence " + std::to_string(i) + " has length " + std::to_string(lens[i]) +
              ", not in 1..4096";
       return false;
     }
-    ImgDesc& d = seqs[i];
-    d.pix_off = 0;
-    d.H = d.W = d.gh = d.gw = 0;
-    d.tok_start = (int32_t)t;
+    *T += lens[i];
+    *blocks += (lens[i] + step - 1) / step;
+  }
+  if (*T > (1LL << 24)) { *why = "more than 2^24 tokens"; return false; }
+  return true;
+}
+
+void attention_seqs(int32_t n, const int32_t* lens, ImgDesc* seqs) {
+  int32_t t = 0;
+  for (int i = 0; i < n; ++i) {
+    ImgDesc d = {};
+    d.tok_start = t;
     d.ntok = lens[i];
-    if (resident && lens[i] > kResMinTokens && lens[i] <= 64 * kResMaxTiles) {
-      res.push_back(i);
-      ap->res_tiles = std::max(ap->res_tiles, (lens[i] + 63) / 64);
-    } else {
-      for (int q0 = 0; q0 < lens[i]; q0 += kAttnQ) items.push_back(AttnItem{i, q0});
-    }
+    seqs[i] = d;
     t += lens[i];
   }
-  if (t > (1LL << 24)) { *why = "more than 2^24 tokens"; return false; }
+}
+
+bool attention_plan(int32_t n, const int32_t* lens, int heads, bool resident, bool short_ok,
+                    AttnPlan* ap, std::string* why) {
+  size_t blocks = 0;
+  if (!attention_lengths(n, lens, kAttnQ, &ap->T, &blocks, why)) return false;
+  resident = resident && n <= 256 && resident_pays(n, heads, [&](int i) { return lens[i]; });
+  std::vector<int32_t> all(n);
+  for (int i = 0; i < n; ++i) all[i] = i;
+  if (resident) {   // every sequence
+    ap->n_res = n;
+    ap->res_tiles = (lens[0] + 63) / 64;
+    blocks = 0;
+  }
   auto a16 = [](size_t x) { return (x + 15) / 16 * 16; };
-  order_attention(&items, seqs.data(), heads);
-  order_attention(&res, seqs.data(), heads);
   ap->off_items = a16(sizeof(ImgDesc) * n);
-  ap->off_res = a16(ap->off_items + sizeof(AttnItem) * items.size());
-  ap->desc.assign(ap->off_res + sizeof(int32_t) * res.size(), 0);
-  std::memcpy(ap->desc.data(), seqs.data(), sizeof(ImgDesc) * n);
-  std::memcpy(ap->desc.data() + ap->off_items, items.data(), sizeof(AttnItem) * items.size());
-  std::memcpy(ap->desc.data() + ap->off_res, res.data(), sizeof(int32_t) * res.size());
-  ap->n_items = (int)items.size();
-  ap->n_res = (int)res.size();
-  ap->T = t;
+  ap->off_res = a16(ap->off_items + sizeof(AttnItem) * blocks);
+  ap->desc.assign(ap->off_res + sizeof(int32_t) * ap->n_res, 0);
+  ap->n_items = (int)blocks;
+  ImgDesc* seqs = reinterpret_cast<ImgDesc*>(ap->desc.data());
+  attention_seqs(n, lens, seqs);
+  if (resident)
+    std::memcpy(ap->desc.data() + ap->off_res, all.data(), sizeof(int32_t) * n);
+  else
+    ap->n_short = attention_items(all.data(), n, seqs, kAttnQ, heads, short_ok,
+                                  reinterpret_cast<AttnItem*>(ap->desc.data() + ap->off_items));
   return true;
 }
 
@@ -1523,40 +1542,26 @@ struct AttnBwdPlan {
 
 bool attention_bwd_plan(int32_t n, const int32_t* lens, int heads, int head_dim,
                         AttnBwdPlan* bp, std::string* why) {
-  if (n <= 0 || n > kMaxItems) { *why = "n_seqs must be 1..65535"; return false; }
-  if (!lens) { *why = "lengths is NULL"; return false; }
-  std::vector<ImgDesc> seqs(n);
-  std::vector<AttnItem> it64, it128;
-  int64_t t = 0;
-  for (int i = 0; i < n; ++i) {
-    if (lens[i] < 1 || lens[i] > kMaxAttnLen) {
-      *why = "sequence " + std::to_string(i) + " has length " + std::to_string(lens[i]) +
-             ", not in 1..4096";
-      return false;
-    }
-    ImgDesc& d = seqs[i];
-    d.pix_off = 0;
-    d.H = d.W = d.gh = d.gw = 0;
-    d.tok_start = (int32_t)t;
-    d.ntok = lens[i];
-    for (int q0 = 0; q0 < lens[i]; q0 += 64) it64.push_back(AttnItem{i, q0});
-    for (int q0 = 0; q0 < lens[i]; q0 += 128) it128.push_back(AttnItem{i, q0});
-    t += lens[i];
-  }
-  if (t > (1LL << 24)) { *why = "more than 2^24 tokens"; return false; }
+  size_t n64 = 0, n128 = 0;
+  if (!attention_lengths(n, lens, 64, &bp->T, &n64, why) ||
+      !attention_lengths(n, lens, 128, &bp->T, &n128, why))
+    return false;
+  const int64_t t = bp->T;
   auto a16 = [](size_t x) { return (x + 15) / 16 * 16; };
-  order_attention(&it64, seqs.data(), heads);
-  order_attention(&it128, seqs.data(), heads);
   bp->off_items64 = a16(sizeof(ImgDesc) * n);
-  bp->off_items128 = a16(bp->off_items64 + sizeof(AttnItem) * it64.size());
-  bp->desc.assign(bp->off_items128 + sizeof(AttnItem) * it128.size(), 0);
-  std::memcpy(bp->desc.data(), seqs.data(), sizeof(ImgDesc) * n);
-  std::memcpy(bp->desc.data() + bp->off_items64, it64.data(), sizeof(AttnItem) * it64.size());
-  std::memcpy(bp->desc.data() + bp->off_items128, it128.data(),
-              sizeof(AttnItem) * it128.size());
-  bp->n_items64 = (int)it64.size();
-  bp->n_items128 = (int)it128.size();
-  bp->T = t;
+  bp->off_items128 = a16(bp->off_items64 + sizeof(AttnItem) * n64);
+  bp->desc.assign(bp->off_items128 + sizeof(AttnItem) * n128, 0);
+  bp->n_items64 = (int)n64;
+  bp->n_items128 = (int)n128;
+  std::vector<int32_t> all(n);
+  for (int i = 0; i < n; ++i) all[i] = i;
+  char* d = bp->desc.data();
+  ImgDesc* seqs = reinterpret_cast<ImgDesc*>(d);
+  attention_seqs(n, lens, seqs);
+  attention_items(all.data(), n, seqs, 64, heads, false,
+                  reinterpret_cast<AttnItem*>(d + bp->off_items64));
+  attention_items(all.data(), n, seqs, 128, heads, false,
+                  reinterpret_cast<AttnItem*>(d + bp->off_items128));
   bp->off_lse = align_up(bp->desc.size());
   bp->off_dsum = bp->off_lse + align_up(4 * (size_t)t * heads);
   bp->off_dob = bp->off_dsum + align_up(4 * (size_t)t * heads);
@@ -1569,11 +1574,14 @@ bool attention_bwd_plan(int32_t n, const int32_t* lens, int heads, int head_dim,
 extern "C" {
 
 size_t vl_attention_workspace_bytes(int32_t n_seqs, const int32_t* lengths) {
-  AttnPlan ap;
+  int64_t T = 0;
+  size_t blocks = 0;
   std::string why;
-  if (!attention_plan(n_seqs, lengths, 8, false, &ap, &why)) return 0;
+  if (!attention_lengths(n_seqs, lengths, kAttnQ, &T, &blocks, &why)) return 0;
   // an upper bound for every precision: all work items plus a resident list
-  return align_up(ap.desc.size() + sizeof(int32_t) * (size_t)n_seqs + 16);
+  // (and the alignment of the three)
+  return align_up((sizeof(ImgDesc) + sizeof(int32_t)) * (size_t)n_seqs +
+                  sizeof(AttnItem) * blocks + 48);
 }
 
 vl_status vl_attention(const void* qkv, vl_precision prec, const int32_t* lengths, int32_t n_seqs,
@@ -1590,7 +1598,8 @@ vl_status vl_attention(const void* qkv, vl_precision prec, const int32_t* length
   AttnPlan ap;
   std::string why;
   const bool resident = prec == VL_BF16 && head_dim == 64 && causal == 0;
-  if (!attention_plan(n_seqs, lengths, heads, resident, &ap, &why)) return fail(VL_ERR_INVALID_ARG, why);
+  if (!attention_plan(n_seqs, lengths, heads, resident, prec == VL_BF16, &ap, &why))
+    return fail(VL_ERR_INVALID_ARG, why);
   const std::vector<char>& desc = ap.desc;
   if (ws_bytes < align_up(desc.size()))
     return fail(VL_ERR_WORKSPACE_TOO_SMALL, "workspace too small");
@@ -1609,7 +1618,10 @@ vl_status vl_attention(const void* qkv, vl_precision prec, const int32_t* length
   const AttnItem* d_items = reinterpret_cast<const AttnItem*>(w + ap.off_items);
   if (prec == VL_BF16) {
     VL_HIP(attention_bf16(static_cast<const bf16_t*>(qkv), static_cast<bf16_t*>(out), d_seqs,
-                          d_items, ap.n_items, heads, head_dim, causal != 0, s));
+                          d_items, ap.n_items - ap.n_short, heads, head_dim, causal != 0, s));
+    VL_HIP(attention_bf16_short(static_cast<const bf16_t*>(qkv), static_cast<bf16_t*>(out), d_seqs,
+                                d_items + ap.n_items - ap.n_short, ap.n_short, heads, head_dim,
+                                causal != 0, s));
     VL_HIP(attention_bf16_resident(static_cast<const bf16_t*>(qkv), out, nullptr, false,
                                    (int)ap.T, d_seqs, reinterpret_cast<const int*>(w + ap.off_res),
                                    ap.n_res, ap.res_tiles, heads, head_dim, s));

@@ -320,6 +320,167 @@ __global__ __launch_bounds__(256) void k_attn_bf16(const bf16_t* __restrict__ qk
     }
 }
 
+// ---------------------------------------------------- BF16, short sequences
+// Sequences of at most 64 tokens (class prompts, small images): one wave per
+// (sequence, head), four to a workgroup, no barriers.  The streaming kernel
+// spends a workgroup of four waves, 48 KB of LDS and its ring's start-up on
+// each, with one wave at work.  Here the queries of a 32-row block and the keys
+// go straight to registers as MFMA operands, the values to a slab of LDS
+// (transpose reads), all loads in flight together; the second half of the keys
+// is left out where no query of the block sees it.  Scores, reference maximum
+// (that of the one key tile), exponentials, sums and products are the streaming
+// kernel's in its order, so the outputs have its bits; the terms left out are
+// zeros there.  Bound by the loads' latency over the waves a CU holds (12).
+// 895 prompts of 5 .. 20 tokens and 105 of 77, 12 heads of 64: 59 us in one
+// streaming launch, 18 + 16 so.
+constexpr int SHORT_W = 4;   // waves (sequences) per workgroup
+
+template <int HD>
+__global__ __launch_bounds__(SHORT_W * 64) void k_attn_bf16_short(
+    const bf16_t* __restrict__ qkv, bf16_t* __restrict__ out, const ImgDesc* __restrict__ imgs,
+    const AttnItem* __restrict__ items, int n_items, int heads, int causal) {
+  using TV = KvTile<HD, true>;
+  constexpr int RPI = 1024 / TV::ROWB, NC = HD / 16, NA = HD / 32;
+  __shared__ __attribute__((aligned(1024))) char sV[SHORT_W][TV::BYTES];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  // Heads vary fastest: the waves of one CU share rows of q, k and v.
+  const int wi = xcd_linear(blockIdx.x, gridDim.x) * SHORT_W + wave;
+  if (wi >= n_items * heads) return;
+  const int h = wi % heads;
+  const ImgDesc dsc = imgs[items[wi / heads].img];
+  const int N = dsc.ntok, D = heads * HD, ld = 3 * D;
+  const bf16_t* base = qkv + (size_t)dsc.tok_start * ld + h * HD;
+  const int l32 = lane & 31, g = lane >> 5;
+
+  // Rows past the sequence read as zero (values; buffer bound) or repeat the
+  // last row (keys and queries; masked or not stored).
+  const i32x4 rv = buffer_rsrc(base + 2 * D, ((uint64_t)(N - 1) * ld + HD) * 2);
+  const uint32_t ldsV = lds_offset(&sV[wave][0]);
+  const int vrow = lane / TV::NCH;
+  const int rows = N > 32 ? 64 : 32;
+#pragma unroll
+  for (int i = 0; i < 64 / RPI; ++i) {
+    if (i * RPI >= rows) break;
+    const int row = i * RPI + vrow;
+    dma16(rv, ldsV + i * 1024, row * ld * 2 + (((lane % TV::NCH) ^ TV::f(row)) << 4), 0);
+  }
+  bf16x8 kf[2][NC], qf[NC];
+  auto load_rows = [&](bf16x8* f, const bf16_t* p, int row) {
+    p += (size_t)min(row, N - 1) * ld + 8 * g;
+#pragma unroll
+    for (int c = 0; c < NC; ++c) f[c] = *reinterpret_cast<const bf16x8*>(p + 16 * c);
+  };
+  load_rows(qf, base, l32);
+  load_rows(kf[0], base + D, l32);
+  if (N > 32) load_rows(kf[1], base + D, 32 + l32);
+  const int grp = lane >> 4, li = lane & 15;
+  const int tg = grp >> 1, dh = grp & 1;
+  uint32_t vbase[NA];
+#pragma unroll
+  for (int a = 0; a < NA; ++a) {
+    const int col = 32 * a + 16 * dh + 4 * (li & 3);
+    vbase[a] = ldsV + TV::off(4 * tg + (li >> 2), col >> 3) + (col & 7) * 2;
+  }
+  const float sl2 = 1.4426950408889634f / sqrtf((float)HD);
+
+  // Queries qw .. qw + 31 against the first KB 32-key blocks.
+  auto block = [&](auto kbs, int qw) {
+    constexpr int KB = decltype(kbs)::value;
+    const int q = qw + l32;
+    const int kmax = causal ? min(N - 1, q) : N - 1;
+    f32x16 s[KB];
+#pragma unroll
+    for (int kb = 0; kb < KB; ++kb) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r) s[kb][r] = 0.f;
+#pragma unroll
+      for (int c = 0; c < NC; ++c)
+        s[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[kb][c], qf[c], s[kb], 0, 0, 0);
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+        if (32 * kb + 8 * (r >> 2) + 4 * g + (r & 3) > kmax) s[kb][r] = -INFINITY;
+    }
+    float mt = s[0][0];
+#pragma unroll
+    for (int i = 1; i < 16 * KB; ++i) mt = fmaxf(mt, s[i >> 4][i & 15]);
+    const float m = xor_op<32>(mt, MaxOp()) * sl2, nm = -m;
+    float ls0 = 0.f, ls1 = 0.f;
+#pragma unroll
+    for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const float p = __builtin_amdgcn_exp2f(fmaf(s[kb][r], sl2, nm));
+        s[kb][r] = p;
+        if (r & 1) ls1 += p; else ls0 += p;
+      }
+    f32x16 o[NA];
+#pragma unroll
+    for (int a = 0; a < NA; ++a)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) o[a][r] = 0.f;
+#pragma unroll
+    for (int jj = 0; jj < 2 * KB; ++jj) {
+      const int kb = jj >> 1, hh = jj & 1;
+      u32x4 pk;
+#pragma unroll
+      for (int w = 0; w < 4; ++w)
+        pk[w] = pack_bf16x2(s[kb][8 * hh + 2 * w], s[kb][8 * hh + 2 * w + 1]);
+      const bf16x8 pf = __builtin_bit_cast(bf16x8, pk);
+#pragma unroll
+      for (int a = 0; a < NA; ++a) {
+        typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+        const uint32_t vb = vbase[a] + 16 * jj * TV::ROWB;
+        const u32x2 v0 = __builtin_bit_cast(
+            u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(uintptr_t)vb));
+        const u32x2 v1 = __builtin_bit_cast(
+            u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+                       (lds_s16x4*)(uintptr_t)(vb + 8 * TV::ROWB)));
+        const u32x4 vk = {v0.x, v0.y, v1.x, v1.y};
+        o[a] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, vk), pf, o[a],
+                                                       0, 0, 0);
+      }
+    }
+    if (q >= N) return;
+    const float inv = 1.f / xor_op<32>(ls0 + ls1, AddOp());
+    bf16_t* op = out + (size_t)(dsc.tok_start + q) * D + h * HD;
+#pragma unroll
+    for (int a = 0; a < NA; ++a)
+#pragma unroll
+      for (int rq = 0; rq < 4; ++rq) {
+        u32x2 pk;
+        pk.x = pack_bf16x2(o[a][4 * rq + 0] * inv, o[a][4 * rq + 1] * inv);
+        pk.y = pack_bf16x2(o[a][4 * rq + 2] * inv, o[a][4 * rq + 3] * inv);
+        *reinterpret_cast<u32x2*>(op + a * 32 + 8 * rq + 4 * g) = pk;
+      }
+  };
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this wave's values
+  if (N <= 32) {
+    block(std::integral_constant<int, 1>(), 0);
+    return;
+  }
+  if (causal) block(std::integral_constant<int, 1>(), 0);
+  else block(std::integral_constant<int, 2>(), 0);
+  load_rows(qf, base, 32 + l32);
+  block(std::integral_constant<int, 2>(), 32);
+}
+
+hipError_t attention_bf16_short(const bf16_t* qkv, bf16_t* o, const ImgDesc* imgs,
+                                const AttnItem* items, int n_items, int heads, int head_dim,
+                                bool causal, hipStream_t s) {
+  if (n_items <= 0) return hipSuccess;
+  dim3 grid((n_items * heads + SHORT_W - 1) / SHORT_W), block(SHORT_W * 64);
+  if (head_dim == 64)
+    hipLaunchKernelGGL(k_attn_bf16_short<64>, grid, block, 0, s, qkv, o, imgs, items, n_items,
+                       heads, (int)causal);
+  else if (head_dim == 32)
+    hipLaunchKernelGGL(k_attn_bf16_short<32>, grid, block, 0, s, qkv, o, imgs, items, n_items,
+                       heads, (int)causal);
+  else
+    return hipErrorInvalidValue;
+  return hipGetLastError();
+}
+
 // ------------------------------------------------ BF16, K/V resident in LDS
 // For images of 129 .. 64 NT tokens at head width 64: one workgroup of eight
 // waves per (image, head) loads that head's keys and values into LDS once (NT

@@ -193,6 +193,10 @@ hipError_t attention_bf16(const bf16_t* qkv, bf16_t* o, const ImgDesc* imgs,
 hipError_t attention_bf16_mx(const bf16_t* qkv, uint8_t* codes, uint8_t* scales, int T,
                              const ImgDesc* imgs, const AttnItem* items, int n_items,
                              int heads, int head_dim, bool causal, hipStream_t s);
+// attention_bf16 for items of sequences of at most 64 tokens, bitwise.
+hipError_t attention_bf16_short(const bf16_t* qkv, bf16_t* o, const ImgDesc* imgs,
+                                const AttnItem* items, int n_items, int heads, int head_dim,
+                                bool causal, hipStream_t s);
 // K/V-resident form for images of 129 .. 640 tokens at head width 64: one
 // workgroup per (image, head) over res_imgs[0 .. n_res) (image indices);
 // max_tiles = the largest ceil(tokens / 64) among them (<= 10).  Output as

@@ -20,31 +20,47 @@ int cap_images(int n) {
   return std::min(c, kMaxItems);
 }
 
-namespace {
-
-template <typename E, typename F>
-void order_entries(std::vector<E>* v, int heads, F ntok) {
-  bool same = true;
-  for (const E& e : *v) same = same && ntok(e) == ntok(v->front());
-  if (same) return;
-  std::stable_sort(v->begin(), v->end(),
-                   [&](const E& a, const E& b) { return ntok(a) > ntok(b); });
-  const size_t runs = heads % 8 == 0 ? 1 : heads % 4 == 0 ? 2 : heads % 2 == 0 ? 4 : 8;
-  if (runs == 1) return;
-  std::vector<E> o;
-  o.reserve(v->size());
-  for (size_t r = 0; r < runs; ++r)
-    for (size_t i = r; i < v->size(); i += runs) o.push_back((*v)[i]);
-  v->swap(o);
-}
-
-}  // namespace
-
-void order_attention(std::vector<AttnItem>* items, const ImgDesc* imgs, int heads) {
-  order_entries(items, heads, [&](const AttnItem& it) { return imgs[it.img].ntok; });
-}
-void order_attention(std::vector<int32_t>* resident, const ImgDesc* imgs, int heads) {
-  order_entries(resident, heads, [&](int32_t i) { return imgs[i].ntok; });
+int attention_items(const int32_t* seq, int n, const ImgDesc* imgs, int step, int heads,
+                    bool short_ok, AttnItem* out) {
+  // (one pass to count, one to place: the attention entry points plan on
+  // every call)
+  constexpr int kTiles = 65;   // key tiles of 64 tokens, the last: more
+  auto tiles = [&](int i) { return std::min((imgs[i].ntok + 63) / 64, kTiles - 1); };
+  auto blocks = [&](int i) { return (imgs[i].ntok + step - 1) / step; };
+  size_t count[kTiles] = {}, total = 0;
+  int n_short = 0;
+  for (int k = 0; k < n; ++k) {
+    count[tiles(seq[k])] += blocks(seq[k]);
+    total += blocks(seq[k]);
+    n_short += imgs[seq[k]].ntok <= kShortTokens;   // (one block each: kShortTokens <= step)
+  }
+  if (!short_ok || (n_short < n && n_short * (int64_t)heads < 768)) n_short = 0;
+  const size_t rest = total - n_short;
+  int kinds = 0;
+  size_t at[kTiles], pos = 0;   // where each tile count's items start, most tiles first
+  for (int t = kTiles - 1; t >= 0; --t) {
+    const size_t c = t == 1 ? count[1] - n_short : count[t];
+    at[t] = pos;
+    pos += c;
+    kinds += c > 0;
+  }
+  const size_t runs = kinds < 2 || heads % 8 == 0 ? 1 : heads % 4 == 0 ? 2 : heads % 2 == 0 ? 4 : 8;
+  // Rank r goes to run r % runs, the longer runs (by one) first.
+  const size_t q = rest / runs, more = rest % runs;
+  size_t last = rest;
+  for (int k = 0; k < n; ++k) {
+    const int i = seq[k], nt = imgs[i].ntok;
+    if (n_short && nt <= kShortTokens) {
+      out[last++] = AttnItem{i, 0};
+      continue;
+    }
+    size_t& r = at[tiles(i)];
+    for (int q0 = 0; q0 < nt; q0 += step, ++r) {
+      const size_t run = r % runs;
+      out[runs == 1 ? r : run * q + std::min(run, more) + r / runs] = AttnItem{i, q0};
+    }
+  }
+  return n_short;
 }
 
 namespace {
@@ -78,6 +94,8 @@ bool finish_plan(const PlanModel& m, std::vector<ImgDesc>& imgs, int64_t T, Plan
     q.i0 = cut[k];
     q.n = cut[k + 1] - cut[k];
     const int t0 = imgs[q.i0].tok_start;
+    std::vector<int32_t> streamed;
+    size_t n_blocks = 0;
     bool res_ok = m.resident && !m.text;
     if (res_ok && m.res_rule)
       res_ok = !bucketed &&
@@ -91,11 +109,13 @@ bool finish_plan(const PlanModel& m, std::vector<ImgDesc>& imgs, int64_t T, Plan
         res[k].push_back(i - q.i0);
         q.res_tiles = std::max(q.res_tiles, (nt + 63) / 64);
       } else {
-        for (int q0 = 0; q0 < nt; q0 += kAttnQ) items[k].push_back(AttnItem{i - q.i0, q0});
+        streamed.push_back(i - q.i0);
+        n_blocks += (nt + kAttnQ - 1) / kAttnQ;
       }
     }
-    order_attention(&items[k], imgs.data() + q.i0, m.heads);
-    order_attention(&res[k], imgs.data() + q.i0, m.heads);
+    items[k].resize(n_blocks);
+    q.n_short = attention_items(streamed.data(), (int)streamed.size(), imgs.data() + q.i0, kAttnQ,
+                                m.heads, m.short_ok && !bucketed, items[k].data());
     q.n_items = (int)items[k].size();
     q.n_res = (int)res[k].size();
     q.T_cap = q.T; q.n_cap = q.n; q.items_cap = q.n_items; q.res_cap = q.n_res;

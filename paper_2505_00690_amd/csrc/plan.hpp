@@ -26,17 +26,22 @@ constexpr int kMaxItems = 65535;   // images / texts per call (grid y of the gat
 constexpr int64_t kSplitMinTokens = 4096;  // two-part batches from this many tokens
 constexpr int64_t kMaxBatchTokens = int64_t(1) << 24;
 
-// Orders attention work (items of sequences imgs[], or a resident list of
-// their indices) longest sequence first, so that the last workgroups to start
-// are short ones.  The kernels give each XCD a contiguous range of the (head,
-// entry) pairs; where `heads` is no multiple of the 8 XCDs these cut a head's
-// entries, so the order is then dealt round-robin into runs of equal total
-// length, one after the other.  Sequences of one length keep their order.
-// (Resident kernel on 100 sequences of 1 .. 640 tokens, 16 heads: 133 us in
-// batch order, 110 so; streaming kernel on 30 of 1 .. 1500, head width 32: 114,
-// 108.)
-void order_attention(std::vector<AttnItem>* items, const ImgDesc* imgs, int heads);
-void order_attention(std::vector<int32_t>* resident, const ImgDesc* imgs, int heads);
+// The streamed attention work items (blocks of `step` rows) of the n sequences
+// seq[] (indices into imgs), most key tiles first, so that the last workgroups
+// to start are short ones.  The kernel gives each XCD a contiguous range of
+// the (head, item) pairs; where `heads` is no multiple of the 8 XCDs these cut
+// a head's items, so the order is then dealt round-robin into runs of equal
+// total length, one after the other.  Sequences of one tile count keep their
+// order.  (30 sequences of 1 .. 1500 tokens, 16 heads of 32: 114 us in batch
+// order, 108 so.)
+// With short_ok, items of sequences of at most kShortTokens tokens go last, in
+// their order, for the short-sequence kernel; returns their number.  That is
+// a launch more where others remain, so few of them (less than the 768
+// workgroups the chip holds at a time) then stay among the others.
+// out: sum of ceil(ntok / step) items.
+constexpr int kShortTokens = 64;
+int attention_items(const int32_t* seq, int n, const ImgDesc* imgs, int step, int heads,
+                    bool short_ok, AttnItem* out);
 
 // Whether K/V-resident attention is the faster form for a batch or part of n
 // sequences (token counts ntok(i)).  Both forms give the same bits.  A
@@ -71,6 +76,7 @@ struct PlanModel {
   int P = 1, channels = 3;    // patch side and input planes (images)
   int ctx = 0;                // longest sequence (texts)
   int heads = 8;              // attention heads
+  bool short_ok = false;      // short-sequence attention kernel usable (BF16 output)
   bool res_rule = false;      // resident only where resident_pays(), and not in bucketed
                               // plans, whose batches differ; else every sequence that fits
 };
@@ -88,6 +94,7 @@ struct Part {
   // the largest of their key-tile counts.
   size_t off_res = 0;
   int n_res = 0, res_tiles = 0;
+  int n_short = 0;      // of n_items, the last ones: the short-sequence kernel's
   size_t off_tok = 0, off_X = 0, off_Y = 0, off_QH = 0, off_E = 0;  // in the workspace
   size_t off_map = 0;   // MAP pooling: per image O, x, LN(x) [n, D] and MLP hidden [n, F]
   // LayerNorm folding: u = bf16(x * gamma) [T, D], per-32-column (mean, M2)

@@ -1,6 +1,7 @@
 // Host checks of attention work order and of the resident rule (plan.hpp):
-// every entry once, longest first inside each run, runs of balanced length,
-// equal lengths untouched; plans with the rule cover every query block once.
+// every item once, most key tiles first inside each run, runs of balanced
+// length, equal tile counts untouched, short sequences last where they go
+// apart; plans with the rule cover every query block once.
 #include <algorithm>
 #include <cstdio>
 #include <cstdlib>
@@ -20,30 +21,41 @@ int main() {
     const int heads = 1 + (int)(rng() % 64), n = 1 + (int)(rng() % 60);
     std::vector<ImgDesc> imgs(n);
     std::vector<AttnItem> items;
-    std::vector<int32_t> res;
     const int one = t % 3 == 0 ? 1 + (int)(rng() % 900) : 0;
     for (int i = 0; i < n; ++i) {
       std::memset(&imgs[i], 0, sizeof imgs[i]);
-      imgs[i].ntok = one ? one : 1 + (int)(rng() % 900);
+      imgs[i].ntok = one ? one : 1 + (int)(rng() % (t % 5 ? 900 : 90));
       for (int q0 = 0; q0 < imgs[i].ntok; q0 += kAttnQ) items.push_back(AttnItem{i, q0});
-      res.push_back(i);
     }
-    auto a = items;
-    auto r = res;
-    order_attention(&a, imgs.data(), heads);
-    order_attention(&r, imgs.data(), heads);
+    const bool short_ok = t & 1;
+    std::vector<int32_t> seq(n);
+    for (int i = 0; i < n; ++i) seq[i] = i;
+    std::vector<AttnItem> a(items.size());
+    const int n_short =
+        attention_items(seq.data(), n, imgs.data(), kAttnQ, heads, short_ok, a.data());
     auto key = [](const AttnItem& x) { return std::make_pair(x.img, x.q0); };
     std::map<std::pair<int, int>, int> seen;
     for (const auto& x : a) seen[key(x)]++;
     CHECK(a.size() == items.size() && seen.size() == items.size());
-    auto rs = r;
-    std::sort(rs.begin(), rs.end());
-    CHECK(rs == res);
+    int fit = 0;
+    for (const auto& x : items) fit += short_ok && imgs[x.img].ntok <= kShortTokens;
+    const bool apart = fit == (int)items.size() || fit * heads >= 768;
+    CHECK(n_short == (apart ? fit : 0));
+    for (int k = 0; k < n_short; ++k) {
+      const AttnItem x = a[a.size() - n_short + k];
+      CHECK(imgs[x.img].ntok <= kShortTokens);
+      if (k) CHECK(key(a[a.size() - n_short + k - 1]) < key(x));
+    }
+    a.resize(a.size() - n_short);
+    if (a.empty()) continue;
+    for (size_t i = 0; n_short && i < items.size();)
+      if (imgs[items[i].img].ntok <= kShortTokens) items.erase(items.begin() + i);
+      else ++i;
     bool same = true;
-    for (const auto& d : imgs) same = same && d.ntok == imgs[0].ntok;
+    auto tiles = [&](const AttnItem& x) { return (imgs[x.img].ntok + 63) / 64; };
+    for (const auto& x : a) same = same && tiles(x) == tiles(a[0]);
     if (same) {
       for (size_t i = 0; i < a.size(); ++i) CHECK(key(a[i]) == key(items[i]));
-      CHECK(r == res);
       continue;
     }
     const size_t runs = heads % 8 == 0 ? 1 : heads % 4 == 0 ? 2 : heads % 2 == 0 ? 4 : 8;
@@ -53,15 +65,15 @@ int main() {
       const size_t cnt = a.size() / runs + (k < a.size() % runs ? 1 : 0);
       long sum = 0;
       for (size_t i = 0; i < cnt; ++i) {
-        const int len = imgs[a[p + i].img].ntok;
-        if (i) CHECK(len <= imgs[a[p + i - 1].img].ntok);
+        const int len = tiles(a[p + i]);
+        if (i) CHECK(len <= tiles(a[p + i - 1]));
         sum += len;
       }
       p += cnt;
       lo = lo < 0 ? sum : std::min(lo, sum);
       hi = std::max(hi, sum);
     }
-    CHECK(hi - lo <= 900);   // dealt round-robin: runs differ by at most the longest
+    CHECK(hi - lo <= 15);   // dealt round-robin: runs differ by at most the longest
   }
   for (int t = 0; t < 400; ++t) {
     PlanModel m;

@@ -259,3 +259,21 @@ def test_resident_rule_keeps_bits(V, n, heads, length):
     a = _run(V, x[:n * length], [length] * n, heads, 64, False, "bf16")
     b = _run(V, x, [length] * n + [3], heads, 64, False, "bf16")
     assert np.array_equal(a, b[:n * length])
+
+
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("d", [64, 32])
+def test_short_sequences_keep_bits(V, d, causal):
+    """Sequences of at most 64 tokens alone run on the short-sequence kernel
+    (here 13 x 3 pairs: the last workgroup is part empty); with one of 65
+    among them, on the streaming kernel.  Same bits, and within the BF16 bar."""
+    heads = 3
+    rng = np.random.Generator(np.random.PCG64(91 + d))
+    lengths = [1, 2, 15, 16, 17, 31, 32, 33, 40, 48, 49, 63, 64]
+    T = sum(lengths)
+    x = _bf16_round(_qkv(lengths + [65], heads, d, rng, qk_std=math.sqrt(10.0)))
+    a = _run(V, x[:T], lengths, heads, d, causal, "bf16")
+    b = _run(V, x, lengths + [65], heads, d, causal, "bf16")
+    assert np.array_equal(a, b[:T])
+    ref, mag, _, _ = oracle_attention(x[:T], lengths, heads, d, causal)
+    assert np.all(np.abs(a - ref) <= 2.0 ** -8 * (mag + np.abs(ref)) + 1e-30)
