@@ -21,7 +21,7 @@ OBJDIR = os.path.join(PKG, "_build")
 
 SOURCES = ["api.cpp", "plan.cpp", "gemm.hip", "gemm_f32.hip", "attention.hip", "elementwise.hip", "contrastive.hip", "train.hip",
            "gemm_kmajor.hip"] + [
-    f"gemm_cfg{i}.hip" for i in [*range(9), *range(13, 17)]] + [f"gemm_mx_cfg{i}.hip" for i in range(9, 13)]
+    f"gemm_cfg{i}.hip" for i in [*range(9), *range(13, 17)]] + [f"gemm_mx_cfg{i}.hip" for i in [*range(9, 13), 17, 18]]
 
 ARCH = "gfx950"
 HIPCC_FLAGS = [

@@ -1848,6 +1848,8 @@ vl_status vl_model_load_tuning(vl_model* m, const char* path) {
       int id = -1;
       for (int c = 0; c < N_GEMM_CFGS; ++c)
         if (e.second.kind == JVal::STR && e.second.str == gemm_cfg_name(c)) id = c;
+      // (the name that configuration had with four waves; same bits)
+      if (e.second.kind == JVal::STR && e.second.str == "MX_128x128_W2x2") id = CFG_MX_128x128_W2x4;
       if (id < 0) return fail(VL_ERR_INVALID_ARG, "unknown tile configuration in " + kv.first);
       t[op][b] = id;
     }

@@ -60,11 +60,15 @@ hipError_t gemm_mx_launch_cfg11(const uint8_t*, const uint8_t*, const uint8_t*, 
                                 int, int, int, int, const EpiArgs&, hipStream_t);
 hipError_t gemm_mx_launch_cfg12(const uint8_t*, const uint8_t*, const uint8_t*, const uint8_t*,
                                 int, int, int, int, const EpiArgs&, hipStream_t);
+hipError_t gemm_mx_launch_cfg17(const uint8_t*, const uint8_t*, const uint8_t*, const uint8_t*,
+                                int, int, int, int, const EpiArgs&, hipStream_t);
+hipError_t gemm_mx_launch_cfg18(const uint8_t*, const uint8_t*, const uint8_t*, const uint8_t*,
+                                int, int, int, int, const EpiArgs&, hipStream_t);
 
 const char* gemm_cfg_name(int cfg) {
   static const char* names[N_GEMM_CFGS] = {"DL_256x256_W2x4", "DL_256x256_W4x2", "DL_256x256_W2x2", "DL_128x128_W2x2", "DL_256x128_W2x2", "DL_128x256_W2x2", "REG_128x128_W2x2", "DL_192x256_W2x4",
-                                           "DL3_160x256_W1x8", "MX_160x256_W1x8", "MX_192x256_W2x4", "MX_128x256_W2x4", "MX_128x128_W2x2",
-                                           "S4_64x32_W2x1", "S4_64x64_W2x2", "S3_64x128_W2x4", "S4_128x128_W2x4"};
+                                           "DL3_160x256_W1x8", "MX_160x256_W1x8", "MX_192x256_W2x4", "MX_128x256_W2x4", "MX_128x128_W2x4",
+                                           "S4_64x32_W2x1", "S4_64x64_W2x2", "S3_64x128_W2x4", "S4_128x128_W2x4", "MX_64x128_W2x4", "MX_64x64_W2x2"};
   return cfg >= 0 && cfg < N_GEMM_CFGS ? names[cfg] : "unknown";
 }
 
@@ -131,20 +135,31 @@ hipError_t gemm_bf16(const bf16_t* A, int lda, const void* B, int ldb, bool b_fp
   return hipErrorInvalidValue;
 }
 
+// The same for MXFP8, by rounds: a full round of `wgs` workgroups per CU takes
+// f + (K / 128) c microseconds, a last one of at most 256 workgroups f1 + (K /
+// 128) c1 (for one workgroup per CU the two are the same).
 int gemm_mx_cfg_heuristic(int M, int N, int K) {
-  (void)K;
-  // Same model as the BF16 heuristic, with the relative tile efficiencies
-  // measured for the MXFP8 kernel on gfx950.
-  struct C { int cfg, bm, bn; double eff; };
-  static const C cands[] = {{CFG_MX_192x256_W2x4, 192, 256, 1.0},
-                            {CFG_MX_160x256_W1x8, 160, 256, 0.95},
-                            {CFG_MX_128x256_W2x4, 128, 256, 0.85},
-                            {CFG_MX_128x128_W2x2, 128, 128, 0.6}};
-  int best = CFG_MX_128x128_W2x2;
+  struct C { int cfg, bm, bn, wgs; double f, c, f1, c1; };
+  // From every configuration's time at M = 65 .. 18 464 and the block shapes
+  // of width 1024.  Rounds of the tiles of 128 rows and more alone, as before
+  // the two small ones and the deeper rings, took up to twice as long (257 x
+  // 1024 x 4096: 27.2 us as 24 tiles of 128 x 128 with two stages, 13.2 us as
+  // 80 of 64 x 64; 577 x 3072 x 1024: 10.9, 7.0 as 240 of 64 x 128; 4616 x
+  // 1024 x 4096: 38.6 with two stages of 128 x 256, 33.3 with three).
+  static const C cands[] = {{CFG_MX_192x256_W2x4, 192, 256, 1, 7.3, 1.2, 7.3, 1.2},
+                            {CFG_MX_160x256_W1x8, 160, 256, 1, 7.0, 1.15, 7.0, 1.15},
+                            {CFG_MX_128x256_W2x4, 128, 256, 1, 6.9, 0.78, 6.9, 0.78},
+                            {CFG_MX_128x128_W2x4, 128, 128, 1, 5.0, 0.54, 5.0, 0.54},
+                            {CFG_MX_64x128_W2x4, 64, 128, 2, 5.2, 0.57, 3.6, 0.367},
+                            {CFG_MX_64x64_W2x2, 64, 64, 2, 4.3, 0.39, 3.2, 0.31}};
+  int best = -1;
   double best_t = 1e300;
   for (const C& c : cands) {
     const long tiles = (long)((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn);
-    const double t = (double)((tiles + 255) / 256) * (c.bm * c.bn) / (65536.0 * c.eff);
+    const long round = 256L * c.wgs, last = tiles % round, kt = K / 128;
+    const double full = c.f + kt * c.c;
+    const double t = tiles / round * full +
+                     (last == 0 ? 0.0 : last <= 256 ? c.f1 + kt * c.c1 : full);
     if (t < best_t) { best_t = t; best = c.cfg; }
   }
   return best;
@@ -159,7 +174,9 @@ hipError_t gemm_mx(const uint8_t* A, const uint8_t* SA, const uint8_t* B, const 
     case CFG_MX_160x256_W1x8: return gemm_mx_launch_cfg9(A, SA, B, SB, M, N, K, op, e, s);
     case CFG_MX_192x256_W2x4: return gemm_mx_launch_cfg10(A, SA, B, SB, M, N, K, op, e, s);
     case CFG_MX_128x256_W2x4: return gemm_mx_launch_cfg11(A, SA, B, SB, M, N, K, op, e, s);
-    case CFG_MX_128x128_W2x2: return gemm_mx_launch_cfg12(A, SA, B, SB, M, N, K, op, e, s);
+    case CFG_MX_128x128_W2x4: return gemm_mx_launch_cfg12(A, SA, B, SB, M, N, K, op, e, s);
+    case CFG_MX_64x128_W2x4: return gemm_mx_launch_cfg17(A, SA, B, SB, M, N, K, op, e, s);
+    case CFG_MX_64x64_W2x2: return gemm_mx_launch_cfg18(A, SA, B, SB, M, N, K, op, e, s);
   }
   return hipErrorInvalidValue;
 }

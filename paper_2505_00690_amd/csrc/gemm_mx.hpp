@@ -51,7 +51,8 @@ __device__ __forceinline__ void wait_vm_le(int n) {
 
 template <int BM, int BN, int WGM, int WGN, int OP, int ST>
 __global__ __launch_bounds__(WGM* WGN * 64)
-__attribute__((amdgpu_waves_per_eu(WGM * WGN / 4, WGM * WGN / 4))) void k_gemm_mx(
+__attribute__((amdgpu_waves_per_eu(BM * BN <= 8192 ? 2 : WGM * WGN / 4,
+                                   BM * BN <= 8192 ? 4 : WGM * WGN / 4))) void k_gemm_mx(
     const uint8_t* __restrict__ A, const uint8_t* __restrict__ SA, const uint8_t* __restrict__ B,
     const uint8_t* __restrict__ SB, int M, int N, int K, int gm, int gn, EpiArgs e) {
   constexpr int EPI = OpEpi<OP>::kind;

@@ -1,0 +1,15 @@
+// MXFP8 GEMM tile configuration MX_64x128_W2x4 (64 x 128 tile, 2 x 4 waves,
+// three K tiles in the ring, two workgroups per CU).
+// One translation unit per configuration so the build compiles them in
+// parallel.
+#include "gemm_mx.hpp"
+
+namespace vl {
+
+hipError_t gemm_mx_launch_cfg17(const uint8_t* A, const uint8_t* SA, const uint8_t* B,
+                               const uint8_t* SB, int M, int N, int K, int op, const EpiArgs& e,
+                               hipStream_t s) {
+  return launch_mx<64, 128, 2, 4, 3>(A, SA, B, SB, M, N, K, op, e, s);
+}
+
+}  // namespace vl

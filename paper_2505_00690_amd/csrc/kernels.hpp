@@ -94,7 +94,7 @@ enum GemmCfg {
   CFG_MX_160x256_W1x8 = 9,
   CFG_MX_192x256_W2x4 = 10,
   CFG_MX_128x256_W2x4 = 11,
-  CFG_MX_128x128_W2x2 = 12,
+  CFG_MX_128x128_W2x4 = 12,
   N_MX_END = 13,
   // BF16 configurations with small tiles and a deep K ring, for products
   // with too few large tiles to fill the chip.
@@ -102,10 +102,16 @@ enum GemmCfg {
   CFG_S4_64x64_W2x2 = 14,
   CFG_S3_64x128_W2x4 = 15,
   CFG_S4_128x128_W2x4 = 16,
-  N_GEMM_CFGS = 17
+  // MXFP8 configurations of the same kind.
+  CFG_MX_64x128_W2x4 = 17,
+  CFG_MX_64x64_W2x2 = 18,
+  N_GEMM_CFGS = 19
 };
 const char* gemm_cfg_name(int cfg);
-inline bool gemm_cfg_is_mx(int cfg) { return cfg >= N_BF16_CFGS && cfg < N_MX_END; }
+inline bool gemm_cfg_is_mx(int cfg) {
+  return (cfg >= N_BF16_CFGS && cfg < N_MX_END) || cfg == CFG_MX_64x128_W2x4 ||
+         cfg == CFG_MX_64x64_W2x2;
+}
 inline bool gemm_cfg_is_bf16(int cfg) {
   return cfg >= 0 && cfg < N_GEMM_CFGS && !gemm_cfg_is_mx(cfg);
 }
