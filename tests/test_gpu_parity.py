@@ -297,6 +297,37 @@ def test_score_heads(V, head, scale, bias, m, dim):
     assert gtop[3] == 5
 
 
+@pytest.mark.parametrize("head", ["softmax", "sigmoid"])
+@pytest.mark.parametrize("m", [4, 1024, 1028, 4096, 4100, 16384, 16388])
+def test_score_row_lengths(V, m, head):
+    """The score rows around the lengths that stay in registers (1024, 4096,
+    16384 texts): FP64 probabilities, and the lowest column among tied maxima
+    (the matching text stands at two columns, in different waves where the
+    row is long enough)."""
+    rng = np.random.Generator(np.random.PCG64(m))
+    e = rng.standard_normal((3, 16))
+    e = (e / np.linalg.norm(e, axis=1, keepdims=True)).astype(np.float32)
+    t = synth.make_texts(m, 16, 3200)
+    first, again = (m - 1) // 3, m - 1
+    t[first] = t[again] = e[1]
+    scale, bias = (50.0, 0.0) if head == "softmax" else (10.0, -10.0)
+    sc = torch.empty((3, m), dtype=torch.float32, device="cuda")
+    top = torch.empty(3, dtype=torch.int32, device="cuda")
+    V.vl_score(torch.from_numpy(e).cuda(), torch.from_numpy(t).cuda(), head, scale, bias, sc, top)
+    torch.cuda.synchronize()
+    ref, _ = O.score(e, t, head, scale, bias)
+    got = sc.cpu().numpy()
+    # |d log p| <= 2 |d logit| (softmax), |d p| <= |d logit| (sigmoid); logits
+    # of unit vectors over 16 products: 16 2^-24 scale, and the exponentials'.
+    bar = (2 * 16 * 2.0 ** -24 * scale + 64 * 2.0 ** -24)
+    if head == "softmax":
+        live = ref > 1e-30
+        assert np.all(np.abs(np.log(got[live]) - np.log(ref[live])) <= bar + m * 2.0 ** -24)
+    else:
+        assert np.all(np.abs(got - ref) <= bar)
+    assert int(top[1]) == first
+
+
 @pytest.mark.parametrize("dim", [4, 252, 260, 1028, 1100])
 def test_logit_tiles_keep_bits(V, dim):
     """The head products' tile sizes (16 x 16 up to 256 tiles, 32 x 32 past
