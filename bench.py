@@ -111,10 +111,11 @@ def _gemm_config(name: str):
     """(op, tile configuration name, kernel source) of a BF16 or MXFP8
     block-GEMM kernel name."""
     import re
-    m = re.search(r"k_gemm_bf16_dl<(\d+), (\d+), (\d+), (\d+), false, (\d), \d, (\d)>", name)
+    m = re.search(r"k_gemm_bf16_dl<(\d+), (\d+), (\d+), (\d+), false, (\d), \d, (\d)(?:, (\d))?>",
+                  name)
     if m and m.group(5) in _OPS:
-        bm, bn, wm, wn, op, st = m.groups()
-        pre = "DL3" if st == "3" else "DL"
+        bm, bn, wm, wn, op, st, loop = m.groups()
+        pre = f"S{st}" if loop == "1" else "DL3" if st == "3" else "DL"   # (1: small tiles)
         return _OPS[op], f"{pre}_{bm}x{bn}_W{wm}x{wn}", "gemm_kernels.hpp"
     m = re.search(r"k_gemm_mx<(\d+), (\d+), (\d+), (\d+), (\d), \d>", name)
     if m and m.group(5) in _OPS:
