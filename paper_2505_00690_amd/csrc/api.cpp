@@ -1529,37 +1529,31 @@ bool attention_plan(int32_t n, const int32_t* lens, int heads, bool resident, bo
   return true;
 }
 
-// The attention backward's descriptor region: sequences, then 64- and
-// 128-token blocks (16-byte aligned); then, each 256-byte aligned, the
+// The attention backward's descriptor region: sequences, then 128-token
+// blocks (16-byte aligned); then, each 256-byte aligned, the
 // log-sum-exp and D = rowsum(dO O) scratch [T, heads] FP32 and dO in BF16
 // [T, heads * head_dim].
 struct AttnBwdPlan {
   std::vector<char> desc;
-  size_t off_items64 = 0, off_items128 = 0, off_lse = 0, off_dsum = 0, off_dob = 0, total = 0;
-  int n_items64 = 0, n_items128 = 0;
+  size_t off_items128 = 0, off_lse = 0, off_dsum = 0, off_dob = 0, total = 0;
+  int n_items128 = 0;
   int64_t T = 0;
 };
 
 bool attention_bwd_plan(int32_t n, const int32_t* lens, int heads, int head_dim,
                         AttnBwdPlan* bp, std::string* why) {
-  size_t n64 = 0, n128 = 0;
-  if (!attention_lengths(n, lens, 64, &bp->T, &n64, why) ||
-      !attention_lengths(n, lens, 128, &bp->T, &n128, why))
-    return false;
+  size_t n128 = 0;
+  if (!attention_lengths(n, lens, 128, &bp->T, &n128, why)) return false;
   const int64_t t = bp->T;
   auto a16 = [](size_t x) { return (x + 15) / 16 * 16; };
-  bp->off_items64 = a16(sizeof(ImgDesc) * n);
-  bp->off_items128 = a16(bp->off_items64 + sizeof(AttnItem) * n64);
+  bp->off_items128 = a16(sizeof(ImgDesc) * n);
   bp->desc.assign(bp->off_items128 + sizeof(AttnItem) * n128, 0);
-  bp->n_items64 = (int)n64;
   bp->n_items128 = (int)n128;
   std::vector<int32_t> all(n);
   for (int i = 0; i < n; ++i) all[i] = i;
   char* d = bp->desc.data();
   ImgDesc* seqs = reinterpret_cast<ImgDesc*>(d);
   attention_seqs(n, lens, seqs);
-  attention_items(all.data(), n, seqs, 64, heads, false,
-                  reinterpret_cast<AttnItem*>(d + bp->off_items64));
   attention_items(all.data(), n, seqs, 128, heads, false,
                   reinterpret_cast<AttnItem*>(d + bp->off_items128));
   bp->off_lse = align_up(bp->desc.size());
@@ -1673,7 +1667,6 @@ vl_status vl_attention_backward(const void* qkv, const void* out, const float* d
   const bool bf = prec == VL_BF16;
   bf16_t* dob = reinterpret_cast<bf16_t*>(w + bp.off_dob);
   VL_HIP(attention_backward(qkv, out, bf, d_out, reinterpret_cast<const ImgDesc*>(w),
-                            reinterpret_cast<const AttnItem*>(w + bp.off_items64), bp.n_items64,
                             reinterpret_cast<const AttnItem*>(w + bp.off_items128),
                             bp.n_items128, heads, head_dim, d_qkv,
                             reinterpret_cast<float*>(w + bp.off_lse),
@@ -1870,9 +1863,7 @@ namespace {
 struct TrainLayer { size_t xin, y1, qkv, o, h, y2, z1, lse, g = 0; };
 struct TrainPlan {
   Plan p;
-  size_t off_items64 = 0;   // 64-token attention blocks (dK / dV), in the descriptor region
-  int n_items64 = 0;
-  size_t off_items128 = 0;  // 128-token attention blocks (dQ), after them
+  size_t off_items128 = 0;  // 128-token attention blocks, in the descriptor region
   int n_items128 = 0;
   int Tp = 0;               // T rounded up to 64 (K of the weight-gradient GEMMs)
   std::vector<TrainLayer> layers;
@@ -1935,17 +1926,13 @@ bool make_train_plan(const vl_model* m, int32_t n, const int32_t* hs, const int3
   Plan& p = tp->p;
   // (2^20 tokens: the transposes' grid spans T / 32 rows of workgroups)
   if (p.T > (1 << 20)) { *why = "training batch exceeds 2^20 tokens"; return false; }
-  // 64- and 128-token blocks of every image for the attention backward
-  std::vector<AttnItem> it, it2;
+  // 128-token blocks of every image for the attention backward
+  std::vector<AttnItem> it2;
   const ImgDesc* imgs = reinterpret_cast<const ImgDesc*>(p.desc.data() + p.parts[0].off_imgs);
-  for (int i = 0; i < n; ++i) {
-    for (int t0 = 0; t0 < imgs[i].ntok; t0 += 64) it.push_back(AttnItem{i, t0});
+  for (int i = 0; i < n; ++i)
     for (int t0 = 0; t0 < imgs[i].ntok; t0 += 128) it2.push_back(AttnItem{i, t0});
-  }
-  tp->n_items64 = (int)it.size();
-  tp->off_items64 = (p.desc_bytes + 15) / 16 * 16;
   tp->n_items128 = (int)it2.size();
-  tp->off_items128 = tp->off_items64 + sizeof(AttnItem) * it.size();
+  tp->off_items128 = (p.desc_bytes + 15) / 16 * 16;
   size_t new_desc = tp->off_items128 + sizeof(AttnItem) * it2.size();
   // Two halves for the forward: the split planner's parts, their descriptor
   // blob appended here.
@@ -1977,7 +1964,6 @@ bool make_train_plan(const vl_model* m, int32_t n, const int32_t* hs, const int3
     p.total += shift;
   }
   p.desc.resize(new_desc, 0);
-  std::memcpy(p.desc.data() + tp->off_items64, it.data(), sizeof(AttnItem) * it.size());
   std::memcpy(p.desc.data() + tp->off_items128, it2.data(), sizeof(AttnItem) * it2.size());
   if (!tp->halves.empty()) std::memcpy(p.desc.data() + tp->off_split, sp.desc.data(), sp.desc_bytes);
   p.desc_bytes = new_desc;
@@ -2431,7 +2417,6 @@ vl_status run_backward_body(vl_model* m, const TrainPlan& tp, const float* pix, 
   const Part& p = tp.p.parts[0];
   const bool f32 = m->prec == VL_FP32, bf = !f32;
   const ImgDesc* d_imgs = reinterpret_cast<const ImgDesc*>(ws + p.off_imgs);
-  const AttnItem* d_items64 = reinterpret_cast<const AttnItem*>(ws + tp.off_items64);
   const AttnItem* d_items128 = reinterpret_cast<const AttnItem*>(ws + tp.off_items128);
   int2* tok = reinterpret_cast<int2*>(ws + p.off_tok);
   const float* X = reinterpret_cast<const float*>(ws + p.off_X);
@@ -2579,9 +2564,8 @@ vl_status run_backward_body(vl_model* m, const TrainPlan& tp, const float* pix, 
     // (BF16: the log-sum-exp the forward kept, and dO also in BF16; FP32:
     // recomputed)
     if ((st = wait(s, kEvWFc1)) != VL_OK) return st;   // FC1's weight gradient read dZ
-    VL_HIP(attention_backward(ws + sv.qkv, ws + sv.o, bf, dY, d_imgs, d_items64, tp.n_items64,
-                              d_items128, tp.n_items128,
-                              m->heads, m->hd, dZ,
+    VL_HIP(attention_backward(ws + sv.qkv, ws + sv.o, bf, dY, d_imgs, d_items128,
+                              tp.n_items128, m->heads, m->hd, dZ,
                               reinterpret_cast<float*>(ws + (bf ? sv.lse : tp.lse)),
                               reinterpret_cast<float*>(ws + tp.dsum), s, bf,
                               bf ? static_cast<bf16_t*>(dOb) : nullptr));

@@ -934,6 +934,339 @@ __global__ __launch_bounds__(256) void k_attn_f32(const float* __restrict__ qkv,
                       o[a][4 * rq + 3] * inv);
 }
 
+// ------------------------------------------------------- FP32 backward
+// On the same instruction, in two kernels, no atomics.  dQ: four waves of 32
+// queries; key and value tiles of 32 tokens stream as above; S^T = K Q^T and
+// dP^T = V dO^T (lane: one query), p against a running reference maximum, dS =
+// p (dP - D), dQ^T += K^T dS^T with dS^T from the registers and K^T read by
+// columns of the key tile, the sum divided at the end; it also writes the
+// log-sum-exp and D = rowsum(dO O).  dK / dV: four waves of 32 keys (lane: one
+// key); query and dO tiles stream with those two values; S = Q K^T, dP = dO
+// V^T, dV^T += dO^T P, dK^T += Q^T dS.  Bound by the matrix pipe (96 and 128
+// MFMAs of 64 cycles per wave and tile at head width 64).  Four images of 197
+// tokens, 12 heads of 64: 331 us as 64 x 64 tiles of FMAs, 86 here; eight of
+// 577, 16 heads: 4330, 501.
+
+// Tiles read by rows and by columns: chunk c of row r at c ^ (r mod NCH).
+template <int HD>
+struct F32Tile {
+  static constexpr int NCH = HD / 4, ROWB = HD * 4, RPI = 1024 / ROWB;
+  static constexpr int LPW = F32_KV / RPI / 4, BYTES = F32_KV * ROWB;
+  // This lane's global offset of load i of its wave (rows of ld floats).
+  __device__ static int goff(int wave, int lane, int i, int ld) {
+    const int row = (wave * LPW + i) * RPI + lane / NCH;
+    return row * ld * 4 + (((lane % NCH) ^ (row & (NCH - 1))) << 4);
+  }
+  // Row operand: element 4c + g (and 4c + 2 + g, 8 bytes on) of row l32 is at
+  // row_base ^ (c << 4).
+  __device__ static int row_base(int l32, int g) {
+    return l32 * ROWB + ((l32 & (NCH - 1)) << 4) + 4 * g;
+  }
+  // Column operand of step r: row R = 8 (r / 4) + 4 g + r % 4, column 32 a +
+  // l32.  R mod NCH = 4 g | x with x = R's other bits, so the chunk is
+  // ((8 a + l32 / 4) ^ 4 g) ^ x.
+  __device__ static int col_base(int a, int l32, int g) {
+    return 4 * g * ROWB + (((8 * a + (l32 >> 2)) ^ (4 * g)) << 4) + (l32 & 3) * 4;
+  }
+  __device__ static int col_off(int base, int r) {
+    const int x = (8 * (r >> 2) + (r & 3)) & (NCH - 1) & ~4;
+    return (base ^ (x << 4)) + (8 * (r >> 2) + (r & 3)) * ROWB;
+  }
+};
+
+// Elements 2s + g of a row of HD floats (the operand of MFMA step s).
+template <int HD>
+__device__ __forceinline__ void f32_operand(float (&f)[HD / 2], const float* p, int g) {
+#pragma unroll
+  for (int c = 0; c < HD / 4; ++c) {
+    const float4 x = *reinterpret_cast<const float4*>(p + 4 * c);
+    f[2 * c] = g ? x.y : x.x;
+    f[2 * c + 1] = g ? x.w : x.z;
+  }
+}
+
+template <int HD>
+__global__ __launch_bounds__(256) void k_attn_bwd_dq_f32(
+    const float* __restrict__ qkv, const float* __restrict__ O, const float* __restrict__ dO,
+    const ImgDesc* __restrict__ imgs, const AttnItem* __restrict__ items, int heads,
+    float* __restrict__ dqkv, float* __restrict__ lse, float* __restrict__ dsum) {
+  using T = F32Tile<HD>;
+  constexpr int NA = HD / 32, LPW = T::LPW;
+  __shared__ __attribute__((aligned(1024))) char sK[F32_ST][T::BYTES];
+  __shared__ __attribute__((aligned(1024))) char sV[F32_ST][T::BYTES];
+  const int n_items = gridDim.x / heads;
+  const int wi = xcd_linear(blockIdx.x, gridDim.x);
+  const AttnItem it = items[wi % n_items];
+  const int h = wi / n_items;
+  const ImgDesc dsc = imgs[it.img];
+  const int N = dsc.ntok;
+  const int D = heads * HD, ld = 3 * D;
+  const float* base = qkv + (size_t)dsc.tok_start * ld + h * HD;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l32 = lane & 31, g = lane >> 5;
+  const int qw = it.q0 + wave * 32;
+  const bool wave_active = qw < N;
+  const int q = qw + l32, qc = min(q, N - 1);
+
+  float qf[HD / 2], df[HD / 2], dsv = 0.f;
+  {
+    const size_t row = (size_t)(dsc.tok_start + qc) * D + h * HD;
+    float of[HD / 2];
+    f32_operand<HD>(qf, base + (size_t)qc * ld, g);
+    f32_operand<HD>(df, dO + row, g);
+    f32_operand<HD>(of, O + row, g);
+#pragma unroll
+    for (int k = 0; k < HD / 2; ++k) dsv = fmaf(df[k], of[k], dsv);
+    dsv = xor_op<32>(dsv, AddOp());
+  }
+  __builtin_amdgcn_s_waitcnt(0x0F70);   // (as above: before the ring's loads)
+
+  const i32x4 rk = buffer_rsrc(base + D, (uint64_t)N * ld * 4);
+  const i32x4 rv = buffer_rsrc(base + 2 * D, (uint64_t)N * ld * 4);
+  int goff[LPW];
+#pragma unroll
+  for (int i = 0; i < LPW; ++i) goff[i] = T::goff(wave, lane, i, ld);
+  const uint32_t ldsK = lds_offset(&sK[0][0]), ldsV = lds_offset(&sV[0][0]);
+  auto issue = [&](int kt, int st) {             // rows past the image: zero or masked
+    const int kb = kt * F32_KV * ld * 4;
+#pragma unroll
+    for (int i = 0; i < LPW; ++i) {
+      const uint32_t lo = st * T::BYTES + (wave * LPW + i) * 1024;
+      dma16(rk, ldsK + lo, goff[i] + kb, 0);
+      dma16(rv, ldsV + lo, goff[i] + kb, 0);
+    }
+  };
+  const int rbase = T::row_base(l32, g);
+  int cbase[NA];
+#pragma unroll
+  for (int a = 0; a < NA; ++a) cbase[a] = T::col_base(a, l32, g);
+
+  const float sc = 1.f / sqrtf((float)HD);
+  float m_run = -INFINITY, l_run = 0.f;
+  f32x16 dq[NA];
+#pragma unroll
+  for (int a = 0; a < NA; ++a)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) dq[a][r] = 0.f;
+  const int KT = (N + F32_KV - 1) / F32_KV;
+  issue(0, 0);
+  if (KT > 1) issue(1, 1);
+  int st = 0;
+  for (int kt = 0; kt < KT; ++kt) {
+    if (kt + 1 < KT) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * LPW) : "memory");
+    else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    lds_barrier();
+    // The stage two ahead held tile kt - 1, whose readers passed the barrier.
+    if (kt + 2 < KT) issue(kt + 2, st == 0 ? 2 : st - 1);
+    const char* tK = sK[st];
+    const char* tV = sV[st];
+    st = st + 1 == F32_ST ? 0 : st + 1;
+    if (!wave_active) continue;
+    f32x16 s, dp;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) s[r] = dp[r] = 0.f;
+#pragma unroll
+    for (int c = 0; c < HD / 4; ++c) {
+      const float* kp = reinterpret_cast<const float*>(tK + (rbase ^ (c << 4)));
+      const float* vp = reinterpret_cast<const float*>(tV + (rbase ^ (c << 4)));
+      s = __builtin_amdgcn_mfma_f32_32x32x2f32(kp[0], qf[2 * c], s, 0, 0, 0);
+      dp = __builtin_amdgcn_mfma_f32_32x32x2f32(vp[0], df[2 * c], dp, 0, 0, 0);
+      s = __builtin_amdgcn_mfma_f32_32x32x2f32(kp[2], qf[2 * c + 1], s, 0, 0, 0);
+      dp = __builtin_amdgcn_mfma_f32_32x32x2f32(vp[2], df[2 * c + 1], dp, 0, 0, 0);
+    }
+    float mt = -INFINITY;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      s[r] = kt * F32_KV + 8 * (r >> 2) + 4 * g + (r & 3) < N ? s[r] * sc : -INFINITY;
+      mt = fmaxf(mt, s[r]);
+    }
+    mt = xor_op<32>(mt, MaxOp());
+    const float m_new = fmaxf(m_run, mt);
+    if (__any(m_new > m_run)) {
+      const float alpha = expf(m_run - m_new);
+      l_run *= alpha;
+#pragma unroll
+      for (int a = 0; a < NA; ++a)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) dq[a][r] *= alpha;
+      m_run = m_new;
+    }
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const float p = expf(s[r] - m_run);
+      l_run += p;
+      s[r] = p * (dp[r] - dsv);
+    }
+#pragma unroll
+    for (int r = 0; r < 16; ++r)
+#pragma unroll
+      for (int a = 0; a < NA; ++a)
+        dq[a] = __builtin_amdgcn_mfma_f32_32x32x2f32(
+            *reinterpret_cast<const float*>(tK + T::col_off(cbase[a], r)), s[r], dq[a], 0, 0, 0);
+  }
+  if (!wave_active || q >= N) return;
+  const float l = xor_op<32>(l_run, AddOp());
+  const float f = sc / l;
+  const size_t row = (size_t)dsc.tok_start + q;
+#pragma unroll
+  for (int a = 0; a < NA; ++a)
+#pragma unroll
+    for (int rq = 0; rq < 4; ++rq)
+      *reinterpret_cast<float4*>(dqkv + row * ld + h * HD + a * 32 + 8 * rq + 4 * g) =
+          make_float4(dq[a][4 * rq] * f, dq[a][4 * rq + 1] * f, dq[a][4 * rq + 2] * f,
+                      dq[a][4 * rq + 3] * f);
+  if (g == 0) {
+    lse[row * heads + h] = m_run + logf(l);
+    dsum[row * heads + h] = dsv;
+  }
+}
+
+template <int HD>
+__global__ __launch_bounds__(256) void k_attn_bwd_dkv_f32(
+    const float* __restrict__ qkv, const float* __restrict__ dO,
+    const ImgDesc* __restrict__ imgs, const AttnItem* __restrict__ items, int heads,
+    const float* __restrict__ lse, const float* __restrict__ dsum, float* __restrict__ dqkv) {
+  using T = F32Tile<HD>;
+  constexpr int NA = HD / 32, LPW = T::LPW;
+  __shared__ __attribute__((aligned(1024))) char sQ[F32_ST][T::BYTES];
+  __shared__ __attribute__((aligned(1024))) char sO[F32_ST][T::BYTES];
+  __shared__ __attribute__((aligned(256))) float sL[F32_ST][64], sD[F32_ST][64];
+  const int n_items = gridDim.x / heads;
+  const int wi = xcd_linear(blockIdx.x, gridDim.x);
+  const AttnItem it = items[wi % n_items];       // it.q0: first key of the block
+  const int h = wi / n_items;
+  const ImgDesc dsc = imgs[it.img];
+  const int N = dsc.ntok;
+  const int D = heads * HD, ld = 3 * D;
+  const float* base = qkv + (size_t)dsc.tok_start * ld + h * HD;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l32 = lane & 31, g = lane >> 5;
+  const int kw = it.q0 + wave * 32;
+  const bool wave_active = kw < N;
+  const int k = kw + l32, kc = min(k, N - 1);
+  float kf[HD / 2], vf[HD / 2];
+  f32_operand<HD>(kf, base + D + (size_t)kc * ld, g);
+  f32_operand<HD>(vf, base + 2 * D + (size_t)kc * ld, g);
+  __builtin_amdgcn_s_waitcnt(0x0F70);
+
+  const i32x4 rq = buffer_rsrc(base, (uint64_t)N * ld * 4);
+  const i32x4 ro = buffer_rsrc(dO + (size_t)dsc.tok_start * D + h * HD, (uint64_t)N * D * 4);
+  const size_t lrow = (size_t)dsc.tok_start * heads + h;
+  const i32x4 rl = buffer_rsrc(lse + lrow, (uint64_t)N * heads * 4);
+  const i32x4 rd = buffer_rsrc(dsum + lrow, (uint64_t)N * heads * 4);
+  int goffQ[LPW], goffO[LPW];
+#pragma unroll
+  for (int i = 0; i < LPW; ++i) {
+    goffQ[i] = T::goff(wave, lane, i, ld);
+    goffO[i] = T::goff(wave, lane, i, D);
+  }
+  const uint32_t ldsQ = lds_offset(&sQ[0][0]), ldsO = lds_offset(&sO[0][0]);
+  const uint32_t ldsL = lds_offset(&sL[0][0]), ldsD = lds_offset(&sD[0][0]);
+  auto issue = [&](int qt, int st) {
+    const int q0 = qt * F32_KV;
+#pragma unroll
+    for (int i = 0; i < LPW; ++i) {
+      const uint32_t lo = st * T::BYTES + (wave * LPW + i) * 1024;
+      dma16(rq, ldsQ + lo, goffQ[i] + q0 * ld * 4, 0);
+      dma16(ro, ldsO + lo, goffO[i] + q0 * D * 4, 0);
+    }
+    if (wave == 0) {
+      dma4(rl, ldsL + st * 256, (q0 + lane) * heads * 4, 0);
+      dma4(rd, ldsD + st * 256, (q0 + lane) * heads * 4, 0);
+    }
+  };
+  const int rbase = T::row_base(l32, g);
+  int cbase[NA];
+#pragma unroll
+  for (int a = 0; a < NA; ++a) cbase[a] = T::col_base(a, l32, g);
+  const float sc = 1.f / sqrtf((float)HD);
+  f32x16 dk[NA], dv[NA];
+#pragma unroll
+  for (int a = 0; a < NA; ++a)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) dk[a][r] = dv[a][r] = 0.f;
+  const int QT = (N + F32_KV - 1) / F32_KV;
+  issue(0, 0);
+  if (QT > 1) issue(1, 1);
+  int st = 0;
+  for (int qt = 0; qt < QT; ++qt) {
+    if (qt + 1 < QT) {
+      if (wave == 0) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * LPW + 2) : "memory");
+      else asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * LPW) : "memory");
+    } else {
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    }
+    lds_barrier();
+    if (qt + 2 < QT) issue(qt + 2, st == 0 ? 2 : st - 1);
+    const char* tQ = sQ[st];
+    const char* tO = sO[st];
+    const float *cL = sL[st], *cD = sD[st];
+    st = st + 1 == F32_ST ? 0 : st + 1;
+    if (!wave_active) continue;
+    f32x16 s, dp;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) s[r] = dp[r] = 0.f;
+#pragma unroll
+    for (int c = 0; c < HD / 4; ++c) {
+      const float* qp = reinterpret_cast<const float*>(tQ + (rbase ^ (c << 4)));
+      const float* op = reinterpret_cast<const float*>(tO + (rbase ^ (c << 4)));
+      s = __builtin_amdgcn_mfma_f32_32x32x2f32(qp[0], kf[2 * c], s, 0, 0, 0);
+      dp = __builtin_amdgcn_mfma_f32_32x32x2f32(op[0], vf[2 * c], dp, 0, 0, 0);
+      s = __builtin_amdgcn_mfma_f32_32x32x2f32(qp[2], kf[2 * c + 1], s, 0, 0, 0);
+      dp = __builtin_amdgcn_mfma_f32_32x32x2f32(op[2], vf[2 * c + 1], dp, 0, 0, 0);
+    }
+    // Query rows past the image are zero (Q, dO, log-sum-exp and D): their p is
+    // 1 and dS 0, against zero rows of dO and Q.
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int qi = 8 * (r >> 2) + 4 * g + (r & 3);
+      s[r] = expf(s[r] * sc - cL[qi]);
+      dp[r] = s[r] * (dp[r] - cD[qi]);
+    }
+#pragma unroll
+    for (int r = 0; r < 16; ++r)
+#pragma unroll
+      for (int a = 0; a < NA; ++a) {
+        const int o = T::col_off(cbase[a], r);
+        dv[a] = __builtin_amdgcn_mfma_f32_32x32x2f32(*reinterpret_cast<const float*>(tO + o),
+                                                     s[r], dv[a], 0, 0, 0);
+        dk[a] = __builtin_amdgcn_mfma_f32_32x32x2f32(*reinterpret_cast<const float*>(tQ + o),
+                                                     dp[r], dk[a], 0, 0, 0);
+      }
+  }
+  if (!wave_active || k >= N) return;
+  float* out = dqkv + ((size_t)dsc.tok_start + k) * ld + D + h * HD;
+#pragma unroll
+  for (int a = 0; a < NA; ++a)
+#pragma unroll
+    for (int rq4 = 0; rq4 < 4; ++rq4) {
+      const int d = a * 32 + 8 * rq4 + 4 * g;
+      *reinterpret_cast<float4*>(out + d) =
+          make_float4(dk[a][4 * rq4] * sc, dk[a][4 * rq4 + 1] * sc, dk[a][4 * rq4 + 2] * sc,
+                      dk[a][4 * rq4 + 3] * sc);
+      *reinterpret_cast<float4*>(out + D + d) =
+          make_float4(dv[a][4 * rq4], dv[a][4 * rq4 + 1], dv[a][4 * rq4 + 2],
+                      dv[a][4 * rq4 + 3]);
+    }
+}
+
+hipError_t attention_backward_f32(const float* qkv, const float* o, const float* dO,
+                                  const ImgDesc* imgs, const AttnItem* items128, int n_items128,
+                                  int heads, int head_dim, float* dqkv, float* lse, float* dsum,
+                                  hipStream_t s) {
+  dim3 grid(n_items128 * heads), block(256);
+  auto launch = [&](auto dq, auto dkv) {
+    hipLaunchKernelGGL(dq, grid, block, 0, s, qkv, o, dO, imgs, items128, heads, dqkv, lse, dsum);
+    hipLaunchKernelGGL(dkv, grid, block, 0, s, qkv, dO, imgs, items128, heads, lse, dsum, dqkv);
+  };
+  if (head_dim == 64) launch(k_attn_bwd_dq_f32<64>, k_attn_bwd_dkv_f32<64>);
+  else if (head_dim == 32) launch(k_attn_bwd_dq_f32<32>, k_attn_bwd_dkv_f32<32>);
+  else return hipErrorInvalidValue;
+  return hipGetLastError();
+}
+
 // ------------------------------------------------ attention pooling (MAP)
 // One learned query per head over all tokens of an image: s_j = q_h . K_jh /
 // sqrt(d), p = softmax_j(s), O_h = sum_j p_j V_jh (FP32 arithmetic).  kv is

@@ -416,202 +416,7 @@ hipError_t gelu_backward(const float* dg, const float* z, void* dz, void* g, boo
 }
 
 // ------------------------------------------------------- attention backward
-// Tiles of 64 queries x 64 keys of one (image, head).  Thread t of a 256-wide
-// workgroup owns row t / 4 of the tile and the quarter t % 4 of its columns;
-// scores are recomputed from Q and K in FP32 (BF16 operands are widened).
-// dq pass: per 64-query block, first the row maximum and sum of
-// exponentials over all keys (log-sum-exp), then dQ; it also writes the
-// log-sum-exp and D = rowsum(dO * O) for the dk/dv pass, which walks all
-// query blocks per 64-key block.  No atomics: every output has one writer.
-constexpr int AB = 64;
-
-template <typename T, int HD>
-__global__ __launch_bounds__(256) void k_attn_bwd_dq(const T* __restrict__ qkv,
-                                                     const T* __restrict__ o,
-                                                     const float* __restrict__ dO,
-                                                     const ImgDesc* __restrict__ imgs,
-                                                     const AttnItem* __restrict__ items, int heads,
-                                                     T* __restrict__ dqkv, float* __restrict__ lse,
-                                                     float* __restrict__ dsum) {
-  constexpr int LD = HD + 1, KQ = HD / 4;
-  __shared__ float sQ[AB][LD], sdO[AB][LD], sK[AB][LD], sV[AB][LD], sS[AB][AB + 1];
-  const AttnItem it = items[blockIdx.x];
-  const int h = blockIdx.y;
-  const ImgDesc d = imgs[it.img];
-  const int N = d.ntok, base = d.tok_start;
-  const int DM = heads * HD, D3 = 3 * DM;
-  const float scale = 1.0f / sqrtf((float)HD);
-  const int tid = threadIdx.x, r = tid >> 2, cq = tid & 3;
-  const int nq = min(AB, N - it.q0);
-  for (int i = tid; i < AB * HD; i += 256) {
-    const int rr = i / HD, k = i - rr * HD;
-    const bool ok = rr < nq;
-    const size_t row = (size_t)(base + it.q0 + rr);
-    sQ[rr][k] = ok ? ldf(qkv, row * D3 + h * HD + k) : 0.f;
-    sdO[rr][k] = ok ? dO[row * DM + h * HD + k] : 0.f;
-    sV[rr][k] = ok ? ldf(o, row * DM + h * HD + k) : 0.f;   // O, for D
-  }
-  __syncthreads();
-  float dsv = 0.f;
-#pragma unroll
-  for (int k = 0; k < KQ; ++k) dsv += sdO[r][cq * KQ + k] * sV[r][cq * KQ + k];
-  dsv = xor_op<1>(dsv, AddOp());
-  dsv = xor_op<2>(dsv, AddOp());
-  __syncthreads();
-  auto load_kv = [&](int k0, int nk, bool with_v) {
-    for (int i = tid; i < AB * HD; i += 256) {
-      const int rr = i / HD, k = i - rr * HD;
-      const size_t row = (size_t)(base + k0 + rr);
-      sK[rr][k] = rr < nk ? ldf(qkv, row * D3 + DM + h * HD + k) : 0.f;
-      if (with_v) sV[rr][k] = rr < nk ? ldf(qkv, row * D3 + 2 * DM + h * HD + k) : 0.f;
-    }
-  };
-  // pass 1: log-sum-exp of the row over all keys of the image
-  float mrow = -INFINITY, lrow = 0.f;
-  for (int k0 = 0; k0 < N; k0 += AB) {
-    const int nk = min(AB, N - k0);
-    load_kv(k0, nk, false);
-    __syncthreads();
-    float sc[16];
-    float tmax = -INFINITY;
-#pragma unroll
-    for (int j = 0; j < 16; ++j) {
-      const int c = cq * 16 + j;
-      float a = 0.f;
-#pragma unroll
-      for (int k = 0; k < HD; ++k) a += sQ[r][k] * sK[c][k];
-      sc[j] = c < nk ? a * scale : -INFINITY;
-      tmax = fmaxf(tmax, sc[j]);
-    }
-    tmax = xor_op<1>(tmax, MaxOp());
-    tmax = xor_op<2>(tmax, MaxOp());
-    const float mnew = fmaxf(mrow, tmax);
-    float ts = 0.f;
-#pragma unroll
-    for (int j = 0; j < 16; ++j) ts += expf(sc[j] - mnew);
-    ts = xor_op<1>(ts, AddOp());
-    ts = xor_op<2>(ts, AddOp());
-    lrow = lrow * expf(mrow - mnew) + ts;
-    mrow = mnew;
-    __syncthreads();
-  }
-  const float lse_r = mrow + logf(lrow);
-  // pass 2: dS and dQ
-  float dq[KQ];
-#pragma unroll
-  for (int k = 0; k < KQ; ++k) dq[k] = 0.f;
-  for (int k0 = 0; k0 < N; k0 += AB) {
-    const int nk = min(AB, N - k0);
-    load_kv(k0, nk, true);
-    __syncthreads();
-#pragma unroll 4
-    for (int j = 0; j < 16; ++j) {
-      const int c = cq * 16 + j;
-      float a = 0.f, b = 0.f;
-#pragma unroll
-      for (int k = 0; k < HD; ++k) {
-        a += sQ[r][k] * sK[c][k];
-        b += sdO[r][k] * sV[c][k];
-      }
-      const float p = c < nk ? expf(a * scale - lse_r) : 0.f;
-      sS[r][c] = p * (b - dsv);
-    }
-    __syncthreads();
-    for (int c = 0; c < nk; ++c) {
-      const float ds = sS[r][c];
-#pragma unroll
-      for (int k = 0; k < KQ; ++k) dq[k] += ds * sK[c][cq * KQ + k];
-    }
-    __syncthreads();
-  }
-  if (r < nq) {
-    const size_t row = (size_t)(base + it.q0 + r);
-#pragma unroll
-    for (int k = 0; k < KQ; ++k) stf(dqkv, row * D3 + h * HD + cq * KQ + k, dq[k] * scale);
-    if (cq == 0) {
-      lse[row * heads + h] = lse_r;
-      dsum[row * heads + h] = dsv;
-    }
-  }
-}
-
-template <typename T, int HD>
-__global__ __launch_bounds__(256) void k_attn_bwd_dkv(const T* __restrict__ qkv,
-                                                      const float* __restrict__ dO,
-                                                      const ImgDesc* __restrict__ imgs,
-                                                      const AttnItem* __restrict__ items, int heads,
-                                                      const float* __restrict__ lse,
-                                                      const float* __restrict__ dsum,
-                                                      T* __restrict__ dqkv) {
-  constexpr int LD = HD + 1, KQ = HD / 4;
-  __shared__ float sK[AB][LD], sV[AB][LD], sQ[AB][LD], sdO[AB][LD];
-  __shared__ float sP[AB][AB + 1], sDS[AB][AB + 1], sL[AB], sD[AB];
-  const AttnItem it = items[blockIdx.x];   // it.q0: first key of the block
-  const int h = blockIdx.y;
-  const ImgDesc d = imgs[it.img];
-  const int N = d.ntok, base = d.tok_start;
-  const int DM = heads * HD, D3 = 3 * DM;
-  const float scale = 1.0f / sqrtf((float)HD);
-  const int tid = threadIdx.x, c = tid >> 2, rq = tid & 3;
-  const int nk = min(AB, N - it.q0);
-  for (int i = tid; i < AB * HD; i += 256) {
-    const int rr = i / HD, k = i - rr * HD;
-    const size_t row = (size_t)(base + it.q0 + rr);
-    sK[rr][k] = rr < nk ? ldf(qkv, row * D3 + DM + h * HD + k) : 0.f;
-    sV[rr][k] = rr < nk ? ldf(qkv, row * D3 + 2 * DM + h * HD + k) : 0.f;
-  }
-  float dk[KQ], dv[KQ];
-#pragma unroll
-  for (int k = 0; k < KQ; ++k) dk[k] = dv[k] = 0.f;
-  for (int q0 = 0; q0 < N; q0 += AB) {
-    const int nq = min(AB, N - q0);
-    for (int i = tid; i < AB * HD; i += 256) {
-      const int rr = i / HD, k = i - rr * HD;
-      const size_t row = (size_t)(base + q0 + rr);
-      sQ[rr][k] = rr < nq ? ldf(qkv, row * D3 + h * HD + k) : 0.f;
-      sdO[rr][k] = rr < nq ? dO[row * DM + h * HD + k] : 0.f;
-    }
-    if (tid < AB) {
-      const size_t row = (size_t)(base + q0 + tid);
-      sL[tid] = tid < nq ? lse[row * heads + h] : 0.f;
-      sD[tid] = tid < nq ? dsum[row * heads + h] : 0.f;
-    }
-    __syncthreads();
-#pragma unroll 4
-    for (int j = 0; j < 16; ++j) {
-      const int r = rq * 16 + j;
-      float a = 0.f, b = 0.f;
-#pragma unroll
-      for (int k = 0; k < HD; ++k) {
-        a += sQ[r][k] * sK[c][k];
-        b += sdO[r][k] * sV[c][k];
-      }
-      const bool ok = r < nq && c < nk;
-      const float p = ok ? expf(a * scale - sL[r]) : 0.f;
-      sP[c][r] = p;
-      sDS[c][r] = p * (b - sD[r]);
-    }
-    __syncthreads();
-    for (int r = 0; r < nq; ++r) {
-      const float p = sP[c][r], ds = sDS[c][r];
-#pragma unroll
-      for (int k = 0; k < KQ; ++k) {
-        dv[k] += p * sdO[r][rq * KQ + k];
-        dk[k] += ds * sQ[r][rq * KQ + k];
-      }
-    }
-    __syncthreads();
-  }
-  if (c < nk) {
-    const size_t row = (size_t)(base + it.q0 + c);
-#pragma unroll
-    for (int k = 0; k < KQ; ++k) {
-      stf(dqkv, row * D3 + DM + h * HD + rq * KQ + k, dk[k] * scale);
-      stf(dqkv, row * D3 + 2 * DM + h * HD + rq * KQ + k, dv[k]);
-    }
-  }
-}
-
+// (FP32: attention_backward_f32.)  No atomics: every output has one writer.
 // ---- MFMA form (BF16 models).  v_mfma_f32_32x32x16_bf16 computes
 // C[i][j] += sum_k A[i][k] B[j][k] over 16 values of k: lane (l32, g) gives
 // A[l32][8g + e] and B[l32][8g + e] (e = 0..7) and receives column j = l32,
@@ -1087,10 +892,9 @@ k_attn_bwd_dkv_mfma(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ d
 
 template <int HD>
 static void launch_attn_bwd_mfma(const void* qkv, const void* o, const float* dO,
-                                 const ImgDesc* imgs, const AttnItem* items64, int n_items64,
-                                 const AttnItem* items128, int n_items128, int heads, void* dqkv,
-                                 float* lse, float* dsum, hipStream_t s, bool lse_given,
-                                 bf16_t* dO_bf16) {
+                                 const ImgDesc* imgs, const AttnItem* items128, int n_items128,
+                                 int heads, void* dqkv, float* lse, float* dsum, hipStream_t s,
+                                 bool lse_given, bf16_t* dO_bf16) {
   dim3 gq(n_items128 * heads), bq(256);
   if (lse_given)
     hipLaunchKernelGGL((k_attn_bwd_dq_mfma<HD, true>), gq, bq, 0, s,
@@ -1104,39 +908,25 @@ static void launch_attn_bwd_mfma(const void* qkv, const void* o, const float* dO
                      dO_bf16, imgs, items128, heads, lse, dsum, static_cast<bf16_t*>(dqkv));
 }
 
-template <typename T, int HD>
-static void launch_attn_bwd(const void* qkv, const void* o, const float* dO, const ImgDesc* imgs,
-                            const AttnItem* items, int n_items, int heads, void* dqkv, float* lse,
-                            float* dsum, hipStream_t s) {
-  dim3 grid(n_items, heads), block(256);
-  hipLaunchKernelGGL((k_attn_bwd_dq<T, HD>), grid, block, 0, s, static_cast<const T*>(qkv),
-                     static_cast<const T*>(o), dO, imgs, items, heads, static_cast<T*>(dqkv), lse,
-                     dsum);
-  hipLaunchKernelGGL((k_attn_bwd_dkv<T, HD>), grid, block, 0, s, static_cast<const T*>(qkv), dO,
-                     imgs, items, heads, lse, dsum, static_cast<T*>(dqkv));
-}
-
 hipError_t attention_backward(const void* qkv, const void* o, bool bf16, const float* dO,
-                              const ImgDesc* imgs, const AttnItem* items64, int n_items,
-                              const AttnItem* items128, int n_items128, int heads, int head_dim,
-                              void* dqkv, float* lse, float* dsum, hipStream_t s, bool lse_given,
-                              bf16_t* dO_bf16) {
-  if (n_items <= 0) return hipSuccess;
+                              const ImgDesc* imgs, const AttnItem* items128, int n_items128,
+                              int heads, int head_dim, void* dqkv, float* lse, float* dsum,
+                              hipStream_t s, bool lse_given, bf16_t* dO_bf16) {
+  if (n_items128 <= 0) return hipSuccess;
   if ((lse_given || dO_bf16) && !bf16) return hipErrorInvalidValue;
-  if (bf16 && (!dO_bf16 || !items128 || n_items128 <= 0)) return hipErrorInvalidValue;
-  if (head_dim == 64) {
-    if (bf16)
-      launch_attn_bwd_mfma<64>(qkv, o, dO, imgs, items64, n_items, items128, n_items128, heads,
-                               dqkv, lse, dsum, s, lse_given, dO_bf16);
-    else launch_attn_bwd<float, 64>(qkv, o, dO, imgs, items64, n_items, heads, dqkv, lse, dsum, s);
-  } else if (head_dim == 32) {
-    if (bf16)
-      launch_attn_bwd_mfma<32>(qkv, o, dO, imgs, items64, n_items, items128, n_items128, heads,
-                               dqkv, lse, dsum, s, lse_given, dO_bf16);
-    else launch_attn_bwd<float, 32>(qkv, o, dO, imgs, items64, n_items, heads, dqkv, lse, dsum, s);
-  } else {
+  if ((bf16 && !dO_bf16) || !items128) return hipErrorInvalidValue;
+  if (!bf16)
+    return attention_backward_f32(static_cast<const float*>(qkv), static_cast<const float*>(o), dO,
+                                  imgs, items128, n_items128, heads, head_dim,
+                                  static_cast<float*>(dqkv), lse, dsum, s);
+  if (head_dim == 64)
+    launch_attn_bwd_mfma<64>(qkv, o, dO, imgs, items128, n_items128, heads, dqkv, lse, dsum, s,
+                             lse_given, dO_bf16);
+  else if (head_dim == 32)
+    launch_attn_bwd_mfma<32>(qkv, o, dO, imgs, items128, n_items128, heads, dqkv, lse, dsum, s,
+                             lse_given, dO_bf16);
+  else
     return hipErrorInvalidValue;
-  }
   return hipGetLastError();
 }
 

@@ -146,6 +146,19 @@ def test_attention_backward_ragged(V, d):
     _check(V, qkv, dout, lengths, heads, d)
 
 
+@pytest.mark.parametrize("d", [64, 32])
+def test_attention_backward_tile_edges(V, d):
+    """Around the 32-token tiles and waves and the 128-token workgroups of the
+    FP32 kernels (and the 64-token tiles of the BF16 ones)."""
+    rng = np.random.Generator(np.random.PCG64(5400 + d))
+    lengths = [1, 31, 32, 33, 63, 64, 65, 96, 97, 127, 128, 129, 161]
+    heads = 3
+    T = sum(lengths)
+    qkv = rng.standard_normal((T, 3 * heads * d))
+    dout = rng.standard_normal((T, heads * d))
+    _check(V, qkv, dout, lengths, heads, d)
+
+
 def test_attention_backward_peaked_scores(V):
     """Scores of standard deviation 10 (Q, K entries of std sqrt(10)): most
     rows of P are dominated by a few keys, so P and dS span many binades."""
