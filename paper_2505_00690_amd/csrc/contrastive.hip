@@ -18,8 +18,8 @@ namespace vl {
 // 4, the 16 columns from 16 (t % 4)), so a matrix of n^2 logits fills the chip
 // in both directions: 1024 pairs are 256 workgroups, where one workgroup per 64
 // columns left 240 CUs idle (97 us for the column sums alone; parts, merge and
-// gradient now take 20 us together).  Latency and
-// launches bound them: 4 MB of logits are read twice.
+// gradient now take 20 us together).  Latency and launches bound them: 4 MB of
+// logits are read twice.
 constexpr int CT = 64;
 
 // Maximum and sum of exponentials (relative to that maximum) of 16 values and
@@ -284,7 +284,14 @@ hipError_t contrastive_loss(const float* E, const float* Tx, int n, int dim, int
   // the padding)
   EpiArgs e;
   e.out = L; e.ldo = n16; e.alpha = scale; e.beta = bias;
-  if ((err = gemm_f32(E, dim, Tx, dim, n, n, dim, OP_LOGITS, e, s)) != hipSuccess) return err;
+  // Up to 512 pairs by the heads' kernel (one round of its 32 x 32 tiles): its
+  // eight chains per logit round less than one, which the scale gradient, a
+  // difference of sums that can be near zero for few pairs, shows (19 pairs of
+  // 768: error 3e-6 -> 5e-7, and 34 us instead of 37).  More pairs: the block
+  // kernel is the faster (1024: 85 us against 93).
+  err = n <= 512 ? gemm_f32_rows(E, dim, Tx, dim, n, n, dim, OP_LOGITS, e, s)
+                 : gemm_f32(E, dim, Tx, dim, n, n, dim, OP_LOGITS, e, s);
+  if (err != hipSuccess) return err;
   const int nt = (n + CT - 1) / CT;
   // The tiles' row and column parts wait in Gt's place (2 nt n pairs, at most a
   // quarter of it and 16 n bytes more), which the gradient kernel fills later.
