@@ -987,6 +987,44 @@ def test_contrastive_loss_and_grads(V, head, scale, bias, n, dim):
     assert abs(db - rdb) <= 1e-4 * max(abs(rdb), 1e-4)
 
 
+@pytest.mark.parametrize("head,scale,bias", [("softmax", 100.0, 0.0), ("sigmoid", 10.0, -10.0)])
+@pytest.mark.parametrize("n", [2, 15, 63, 64, 65, 129, 512, 513])
+def test_contrastive_tile_edges(V, head, scale, bias, n):
+    """The losses around the 64 x 64 logit tiles and either side of the switch
+    between the logit kernels (512 pairs), against the oracle.  Bars from the
+    arithmetic: a logit and a log-sum-exp are off by at most d = (dim + 8)
+    2^-24 (scale + |bias|), a probability p by 2 d p + 2^-22, so dL/dl by
+    (2 d (p + q) + 2^-21) / 2n (sigmoid: (d / 4 + 2^-22) / n), and the
+    gradients by scale times that against |e| or |t|, plus 1e-5 relative for
+    their own products; the loss by 2 d."""
+    dim = 32
+    rng = np.random.Generator(np.random.PCG64(190 + n))
+    e, t = rng.standard_normal((2, n, dim))
+    t += 0.5 * e
+    e, t = (x / np.linalg.norm(x, axis=1, keepdims=True) for x in (e, t))
+    e32, t32 = e.astype(np.float32), t.astype(np.float32)
+    loss, de, dt, dsb = V.vl_contrastive_loss(torch.from_numpy(e32).cuda(),
+                                              torch.from_numpy(t32).cuda(), head, scale, bias)
+    torch.cuda.synchronize()
+    ref_l = O.contrastive_loss(e32, t32, head, scale, bias)
+    rde, rdt, rds, rdb = O.contrastive_grads(e32, t32, head, scale, bias)
+    d = (dim + 8) * 2.0 ** -24 * (scale + abs(bias))
+    l = O.logits(e32, t32, scale, bias)
+    if head == "softmax":
+        dg = (2 * d * (O.softmax(l, axis=1) + O.softmax(l, axis=0)) + 2.0 ** -21) / (2 * n)
+    else:
+        dg = np.full((n, n), (d / 4 + 2.0 ** -22) / n)
+    assert abs(float(loss.cpu()[0]) - ref_l) <= 2 * d * (1 if head == "softmax" else n)
+    for got, ref, bar in ((de, rde, scale * dg @ np.abs(t)), (dt, rdt, scale * dg.T @ np.abs(e))):
+        g = got.cpu().numpy().astype(np.float64)
+        size = np.abs(ref) + np.abs(ref).max()
+        assert np.all(np.abs(g - ref) <= bar + 1e-5 * size)
+    ds, db = dsb.cpu().numpy().astype(np.float64)
+    cos = np.abs(e @ t.T)
+    assert abs(ds - rds) <= (dg * (cos + d)).sum() + 1e-5 * abs(rds)
+    assert abs(db - rdb) <= dg.sum() + 1e-5 * abs(rdb)
+
+
 def test_map_pool_two_part_split_bitwise(V):
     """Attention pooling runs per part: a batch above the split threshold
     gives the same bits as one part."""
