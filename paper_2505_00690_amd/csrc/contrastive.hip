@@ -284,13 +284,12 @@ hipError_t contrastive_loss(const float* E, const float* Tx, int n, int dim, int
   // the padding)
   EpiArgs e;
   e.out = L; e.ldo = n16; e.alpha = scale; e.beta = bias;
-  // Up to 512 pairs by the heads' kernel (one round of its 32 x 32 tiles): its
-  // eight chains per logit round less than one, which the scale gradient, a
-  // difference of sums that can be near zero for few pairs, shows (19 pairs of
-  // 768: error 3e-6 -> 5e-7, and 34 us instead of 37).  More pairs: the block
-  // kernel is the faster (1024: 85 us against 93).
-  err = n <= 512 ? gemm_f32_rows(E, dim, Tx, dim, n, n, dim, OP_LOGITS, e, s)
-                 : gemm_f32(E, dim, Tx, dim, n, n, dim, OP_LOGITS, e, s);
+  // One kernel for every n, so a pair's logit is the same chain of fused
+  // multiply-adds in every batch (the heads' kernel, with eight chains, is 3 us
+  // faster up to 512 pairs, 34 against 37; but other last bits of the logits,
+  // some 1e-7 of the gradients here, come out of a training step's BF16
+  // backward as 4e-4 of its weight gradients).
+  err = gemm_f32(E, dim, Tx, dim, n, n, dim, OP_LOGITS, e, s);
   if (err != hipSuccess) return err;
   const int nt = (n + CT - 1) / CT;
   // The tiles' row and column parts wait in Gt's place (2 nt n pairs, at most a
