@@ -23,7 +23,8 @@ namespace vl {
 constexpr int CT = 64;
 
 // Maximum and sum of exponentials (relative to that maximum) of 16 values and
-// the three other threads of the row.
+// the three other threads of the row.  A NaN makes the sum NaN, also where it
+// is the only value in range (the maximum, which skips NaN, is -inf then).
 __device__ __forceinline__ float2 lse_part(const float (&v)[16]) {
   float mx = v[0];
 #pragma unroll
@@ -31,10 +32,9 @@ __device__ __forceinline__ float2 lse_part(const float (&v)[16]) {
   mx = xor_op<1>(mx, MaxOp());
   mx = xor_op<2>(mx, MaxOp());
   float s = 0.f;
-  if (mx > -INFINITY) {   // else no value in range (or none above -inf)
+  // (no value in range, or none above -inf: 0)
 #pragma unroll
-    for (int j = 0; j < 16; ++j) s += expf(v[j] - mx);
-  }
+  for (int j = 0; j < 16; ++j) s += mx == -INFINITY && v[j] == mx ? 0.f : expf(v[j] - mx);
   s = xor_op<1>(s, AddOp());
   s = xor_op<2>(s, AddOp());
   return make_float2(mx, s);
@@ -131,6 +131,9 @@ __global__ __launch_bounds__(256) void k_lse_merge(const float2* __restrict__ ro
       s *= expf(mx - m);
 #pragma unroll
       for (int u = 0; u < 4; ++u) s += v[u].y * expf(v[u].x - m);
+    } else {   // sums of 0, or NaN
+#pragma unroll
+      for (int u = 0; u < 4; ++u) s += v[u].y;
     }
     mx = m;
   }

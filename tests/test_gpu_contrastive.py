@@ -34,3 +34,34 @@ def test_logit_is_one_ascending_chain_at_every_batch_size(V, n, big, one, minus)
                                             0.0)
     assert float(loss.cpu()[0]) == pytest.approx(n * math.log(2.0), rel=1e-4)
     assert float(dsb.cpu()[1]) == pytest.approx(0.5 * n - 1.0, abs=1e-4 * n)
+
+
+@pytest.mark.parametrize("n,row", [(1, 0), (64, 63), (65, 64), (65, 3), (130, 129), (1025, 1024)])
+@pytest.mark.parametrize("where", ["emb", "texts"])
+def test_softmax_nan_reaches_every_gradient(V, n, row, where):
+    """A NaN embedding or text is in every log-sum-exp of the other side (and
+    makes its own NaN), so the softmax loss and all gradients are NaN; also
+    where its logits are the only ones of their 64 x 64 tile's rows (the last
+    text of 65)."""
+    g = torch.Generator().manual_seed(7 * n + row)
+    e, t = (torch.nn.functional.normalize(torch.randn(n, 32, generator=g), dim=1)
+            for _ in range(2))
+    (e if where == "emb" else t)[row, 5] = float("nan")
+    loss, de, dt, dsb = V.vl_contrastive_loss(e.cuda(), t.cuda(), "softmax", 10.0, 0.0)
+    for x in (loss, de, dt, dsb[:1]):
+        assert bool(torch.isnan(x).all())
+
+
+@pytest.mark.parametrize("n", [65, 130])
+def test_sigmoid_nan_stays_in_its_column(V, n):
+    """Sigmoid head: a NaN text makes the loss, every dL/d(embedding) and its
+    own gradient NaN; the other texts' gradients do not depend on it."""
+    g = torch.Generator().manual_seed(n)
+    e, t = (torch.nn.functional.normalize(torch.randn(n, 32, generator=g), dim=1)
+            for _ in range(2))
+    ref = V.vl_contrastive_loss(e.cuda(), t.cuda(), "sigmoid", 10.0, -10.0)[2].cpu().numpy()
+    t[n - 1] = float("nan")
+    loss, de, dt, _ = V.vl_contrastive_loss(e.cuda(), t.cuda(), "sigmoid", 10.0, -10.0)
+    assert bool(torch.isnan(loss).all()) and bool(torch.isnan(de).all())
+    assert bool(torch.isnan(dt[n - 1]).all())
+    assert np.array_equal(dt[:n - 1].cpu().numpy(), ref[:n - 1])
