@@ -693,6 +693,9 @@ class Encoder:
     def set_tuning(self, named: dict) -> None:
         """Inverse of tuning(): {op: {bucket: config name}}."""
         ids = {vl_gemm_config_name(i): i for i in range(vl_gemm_config_count())}
+        # (the name it had with four waves, which tables kept by a program may
+        # hold; vl_model_load_tuning reads it in files)
+        ids["MX_128x128_W2x2"] = ids["MX_128x128_W2x4"]
         table = [[-1] * VL_N_M_BUCKETS for _ in range(VL_N_GEMM_OPS)]
         for op, row in named.items():
             for b, name in row.items():

@@ -228,3 +228,22 @@ def test_binding_checks_buffer_sizes_before_the_call(V):
     with pytest.raises(ValueError, match="emb_out"):
         V.vl_encode_texts(None, torch.zeros(9, dtype=torch.int32), [5, 4], torch.zeros((3, 128)),
                           ws)
+
+
+def test_tables_of_earlier_configuration_names_still_load(V, monkeypatch):
+    """A table kept by a program from Encoder.tuning() stays valid: every name
+    that a configuration has had maps to its id."""
+    seen = []
+    monkeypatch.setattr(V, "vl_model_set_tuning", lambda handle, table: seen.append(table))
+    enc = V.Encoder.__new__(V.Encoder)
+    enc.handle = None
+    names = ["DL_256x256_W2x4", "DL_256x256_W4x2", "DL_256x256_W2x2", "DL_128x128_W2x2",
+             "DL_256x128_W2x2", "DL_128x256_W2x2", "REG_128x128_W2x2", "DL_192x256_W2x4",
+             "DL3_160x256_W1x8", "MX_160x256_W1x8", "MX_192x256_W2x4", "MX_128x256_W2x4",
+             "MX_128x128_W2x2"]
+    V.Encoder.set_tuning(enc, {"fc1_gemm": {str(b): name for b, name in enumerate(names)}})
+    row = seen[0][V.GEMM_OPS.index("fc1_gemm")]
+    assert row[:len(names)] == list(range(len(names)))
+    assert set(row[len(names):]) == {-1}
+    with pytest.raises(KeyError):
+        V.Encoder.set_tuning(enc, {"fc1_gemm": {"0": "MX_1x1_W1x1"}})
