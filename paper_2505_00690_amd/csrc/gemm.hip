@@ -190,22 +190,22 @@ hipError_t gemm_mx(const uint8_t* A, const uint8_t* SA, const uint8_t* B, const 
 // order, and wave w holds chains w and w + 4.  An output is computed the same
 // way whatever M, N and RT are, so a row's result does not depend on the
 // other rows of the batch.  256 K values of the tile's rows are one stage of
-// LDS, streamed by direct-to-LDS loads of a whole 1 KB row each: RT = 1 keeps
-// 4 stages, RT = 2 two, 133 KB both.  (Operands loaded straight into
-// registers need 16-byte pieces of 16 rows per instruction: scores of 1000 x
-// 1000 over K = 512 took 39 us against 26; the vector-ALU kernel before this
-// one, with the same sums, 58 us.)
+// LDS, streamed by direct-to-LDS loads of a whole 1 KB row each, NS stages in
+// flight.  RT = 2 with two stages, and RT = 1 with four, take 133 KB: a
+// workgroup to a CU.  RT = 1 with two lets two share it.  (Operands loaded
+// straight into registers need 16-byte pieces of 16 rows per instruction:
+// scores of 1000 x 1000 over K = 512 took 39 us against 26; the vector-ALU
+// kernel before this one, with the same sums, 58 us.)
 constexpr int FR_KC = 256;                    // K values per stage
 constexpr int FR_LD = FR_KC + 4;              // LDS row: rows 4 banks apart
-constexpr int64_t kRows16Tiles = 256;
-
-template <int OP, int RT>
+template <int OP, int RT, int NS>
 __global__ __launch_bounds__(256) void k_gemm_f32_rows(const float* __restrict__ A, int lda,
                                                        const float* __restrict__ B, int ldb,
                                                        int M, int N, int K, EpiArgs e) {
   constexpr int EPI = OpEpi<OP>::kind;
-  constexpr int T = 16 * RT, NS = 4 / RT;     // tile side, stages
+  constexpr int T = 16 * RT;                  // tile side
   constexpr int LPW = T / 2;                  // rows (loads) per wave and stage
+  static_assert(NS >= 2 && NS <= 4, "stages");
   __shared__ __attribute__((aligned(16))) float smem[NS * 2 * T * FR_LD];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -302,19 +302,25 @@ __global__ __launch_bounds__(256) void k_gemm_f32_rows(const float* __restrict__
 hipError_t gemm_f32_rows(const float* A, int lda, const float* B, int ldb, int M, int N, int K,
                          int op, const EpiArgs& e, hipStream_t s) {
   if (M <= 0) return hipSuccess;
+  // 16 x 16 tiles as long as they are one round.  Beyond that 32 x 32 tiles,
+  // which read each operand half as often; but up to 16 rows half of such a
+  // tile is padding, and small tiles, two workgroups to a CU, are faster (1 x
+  // 20 000 over K = 512: 14.9 us in 32 x 32 tiles, 13.5 in 16 x 16 with four
+  // stages, 9.7 so, the copy rate; 11.3 on the vector ALU.  16 x 8000: 5.6, 5.7,
+  // 4.2; 24 x 8000: 5.7 in 32 x 32, 7.1 in 16 x 16).
   auto tiles = [&](int t) { return (int64_t)((N + t - 1) / t) * ((M + t - 1) / t); };
-  const bool small = tiles(16) <= kRows16Tiles;
+  const bool one_round = tiles(16) <= 256, small = one_round || M <= 16;
   const int64_t blocks = tiles(small ? 16 : 32);
   if (blocks > INT32_MAX) return hipErrorInvalidValue;
   dim3 grid((unsigned)blocks), block(256);
-#define VL_GEMM_CASE(OP)                                                                      \
-  case OP:                                                                                    \
-    if (small)                                                                                \
-      hipLaunchKernelGGL((k_gemm_f32_rows<OP, 1>), grid, block, 0, s, A, lda, B, ldb, M, N, K, \
-                         e);                                                                  \
-    else                                                                                      \
-      hipLaunchKernelGGL((k_gemm_f32_rows<OP, 2>), grid, block, 0, s, A, lda, B, ldb, M, N, K, \
-                         e);                                                                  \
+  auto launch = [&](auto k) {
+    hipLaunchKernelGGL(k, grid, block, 0, s, A, lda, B, ldb, M, N, K, e);
+  };
+#define VL_GEMM_CASE(OP)                              \
+  case OP:                                            \
+    if (one_round) launch(k_gemm_f32_rows<OP, 1, 4>); \
+    else if (small) launch(k_gemm_f32_rows<OP, 1, 2>); \
+    else launch(k_gemm_f32_rows<OP, 2, 2>);           \
     break;
   switch (op) {
     VL_GEMM_CASE(OP_QKV)
