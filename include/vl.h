@@ -274,14 +274,20 @@ vl_status vl_encode_texts(vl_model* m, const int32_t* ids_dev, const int32_t* le
  *                   LayerNorm time falls but the four GEMMs lose more, ~5 %
  *                   slower per step, hence off.)  Changing it drops cached
  *                   graphs.
- *   VL_OPT_ATTN_RESIDENT : on by default (BF16 attention at head width 64,
- *                   image towers).  Images of 129 .. 640 tokens run their
- *                   attention with one workgroup per (image, head) that
- *                   loads the head's keys and values into LDS once and
- *                   serves every query of the image from them; other images
- *                   stream key / value tiles per block of 128 queries.  Both
- *                   forms give the same bits.  Changing it drops cached
- *                   graphs.
+ *   VL_OPT_ATTN_RESIDENT : how BF16 attention at head width 64 runs in image
+ *                   towers (inference and the training forward).  An image
+ *                   of 129 .. 640 tokens can run with one workgroup per
+ *                   (image, head) that loads the head's keys and values into
+ *                   LDS once and serves every query of the image from them;
+ *                   other images stream key / value tiles per block of 128
+ *                   queries.  0 = stream all; 1 = every image that fits runs
+ *                   resident; 2 (default) = resident only where that is
+ *                   the faster form on MI355X: all images of a part have
+ *                   the same number, 7 .. 10, of 64-token tiles, their
+ *                   (image, head) pairs number 224 .. 256, and the graph
+ *                   is not a capacity bucket's.  All give the same bits.
+ *                   Changing it drops cached graphs and changes what
+ *                   vl_encode_workspace_bytes returns.
  *   VL_OPT_GRAPH_BUCKETS : on by default.  0 = key every graph on the exact
  *                   call, also for the models that would plan capacity
  *                   buckets (a fixed-shape workload then launches grids of

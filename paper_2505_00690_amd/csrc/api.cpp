@@ -126,9 +126,10 @@ struct vl_model {
   // models; VL_OPT_FUSED_LN, off by default: on MI355X the extra epilogue
   // output costs the GEMMs more than the standalone LayerNorms take).
   bool fused_ln = false;
-  // K/V-resident attention for images of 129 .. 640 tokens (BF16 attention,
-  // head width 64, not causal; VL_OPT_ATTN_RESIDENT, on by default).
-  bool attn_resident = true;
+  // K/V-resident attention (BF16 attention, head width 64, not causal;
+  // VL_OPT_ATTN_RESIDENT): never, every image of 129 .. 640 tokens, or (default)
+  // where resident_pays().
+  enum { RES_OFF = 0, RES_ON = 1, RES_RULE = 2 } attn_resident = RES_RULE;
   // Graph replay per capacity bucket where the model supports it
   // (VL_OPT_GRAPH_BUCKETS, on by default).
   bool graph_buckets = true;
@@ -213,7 +214,7 @@ PlanModel plan_model(const vl_model* m) {
   pm.text = m->text;
   pm.split = m->split && m->prec != VL_FP32;
   pm.heads = m->heads;
-  pm.res_rule = true;
+  pm.res_rule = m->attn_resident == vl_model::RES_RULE;
   pm.short_ok = m->prec == VL_BF16 || m->prec == VL_FP8W_BF16A;
   pm.resident = m->attn_resident && m->prec != VL_FP32 && m->hd == 64 && !m->text;
   pm.map_pool = !m->text && m->cfg.pool == VL_POOL_MAP;
@@ -977,7 +978,9 @@ vl_status vl_model_set_option(vl_model* m, vl_option opt, int64_t value) {
       return VL_OK;
     case VL_OPT_ATTN_RESIDENT:
       destroy_graphs(m);
-      m->attn_resident = value != 0;
+      m->attn_resident = value == 0                   ? vl_model::RES_OFF
+                         : value == vl_model::RES_RULE ? vl_model::RES_RULE
+                                                       : vl_model::RES_ON;
       return VL_OK;
     case VL_OPT_GRAPH_BUCKETS:
       destroy_graphs(m);
@@ -1462,8 +1465,8 @@ constexpr int kMaxAttnLen = 4096;  // longest sequence vl_attention accepts
 
 // Descriptor blob of a vl_attention call: sequence descriptors, the
 // 128-query work items, then the sequences that run K/V-resident (each part
-// 16-byte aligned), as the encoder lays them out.  resident: whether
-// sequences of 129 .. 640 tokens go to the resident kernel.
+// 16-byte aligned), as the encoder lays them out.  resident: whether the call
+// may use the resident kernel; where resident_pays() it takes every sequence.
 struct AttnPlan {
   std::vector<char> desc;
   size_t off_items = 0, off_res = 0;

@@ -203,8 +203,9 @@ hipError_t attention_bf16_mx(const bf16_t* qkv, uint8_t* codes, uint8_t* scales,
 hipError_t attention_bf16_short(const bf16_t* qkv, bf16_t* o, const ImgDesc* imgs,
                                 const AttnItem* items, int n_items, int heads, int head_dim,
                                 bool causal, hipStream_t s);
-// K/V-resident form for images of 129 .. 640 tokens at head width 64: one
-// workgroup per (image, head) over res_imgs[0 .. n_res) (image indices);
+// K/V-resident form for images of 129 .. 640 tokens at head width 64 (when
+// it is used: resident_pays() and VL_OPT_ATTN_RESIDENT): one workgroup per
+// (image, head) over res_imgs[0 .. n_res) (image indices);
 // max_tiles = the largest ceil(tokens / 64) among them (<= 10).  Output as
 // attention_bf16 (mx = false) or attention_bf16_mx (mx = true), bitwise.
 // With bc: images [0, bc->n_res) of a grid sized for n_res.
@@ -292,16 +293,19 @@ hipError_t gelu_backward(const float* dg, const float* z, void* dz, void* g, boo
 // dQKV [T, 3D] of the attention of every image: items128 are (image, first
 // token) blocks of 128 tokens; lse and dsum [T, heads] are scratch, except
 // that with lse_given (BF16) lse already holds the forward's log-sum-exp
-// (attention_bf16's lse_out) and is only read.  BF16 models also pass dO
-// rounded to BF16 (dO_bf16 [T, D]), from which the dK/dV pass loads its tiles.
-hipError_t attention_backward_f32(const float* qkv, const float* o, const float* dO,
-                                  const ImgDesc* imgs, const AttnItem* items128, int n_items128,
-                                  int heads, int head_dim, float* dqkv, float* lse, float* dsum,
-                                  hipStream_t s);
+// (attention_bf16's lse_out) and is only read.  BF16 also takes dO_bf16 [T,
+// D], from which the dK/dV pass loads its tiles: with lse_given it holds dO
+// rounded to BF16 and is only read, otherwise it is scratch that the dQ pass
+// fills.
 hipError_t attention_backward(const void* qkv, const void* o, bool bf16, const float* dO,
                               const ImgDesc* imgs, const AttnItem* items128, int n_items128,
                               int heads, int head_dim, void* dqkv, float* lse, float* dsum,
                               hipStream_t s, bool lse_given = false, bf16_t* dO_bf16 = nullptr);
+// Its FP32 form.
+hipError_t attention_backward_f32(const float* qkv, const float* o, const float* dO,
+                                  const ImgDesc* imgs, const AttnItem* items128, int n_items128,
+                                  int heads, int head_dim, float* dqkv, float* lse, float* dsum,
+                                  hipStream_t s);
 // Pooling head: de, z [n, *] scratch, the class rows of dX, and the
 // gradients of the projection and the final LayerNorm (pg, pb [n, D] and
 // part [ceil(n / kColRows), D] scratch).

@@ -78,7 +78,8 @@ struct PlanModel {
   int heads = 8;              // attention heads
   bool short_ok = false;      // short-sequence attention kernel usable (BF16 output)
   bool res_rule = false;      // resident only where resident_pays(), and not in bucketed
-                              // plans, whose batches differ; else every sequence that fits
+                              // plans, whose batches differ (VL_OPT_ATTN_RESIDENT 2, the
+                              // default); else every sequence that fits (1)
 };
 
 // A batch runs as one or two parts.  A part is a run of consecutive images
