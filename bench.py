@@ -539,7 +539,8 @@ def main(argv=None) -> int:
                     default=None, help="print the GEMM traffic records of two rocprofv3 "
                     "--pmc runs (FETCH_SIZE, WRITE_SIZE) and exit")
     ap.add_argument("--no-attn-resident", action="store_true",
-                    help="stream key / value tiles per 128-query block for every image")
+                    help="stream key / value tiles per 128-query block for every image "
+                         "(default: K/V-resident where that is faster)")
     ap.add_argument("--fused-ln", action="store_true",
                     help="fold the LayerNorms into the GEMMs (measured slower; off by default)")
     ap.add_argument("--no-train", action="store_true",

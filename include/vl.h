@@ -501,7 +501,7 @@ vl_status vl_attention(const void* qkv_dev, vl_precision prec, const int32_t* le
  *              per-query log-sum-exp and rowsum(dO * O), dO in BF16).
  * All device pointers 16-byte aligned.  The BF16 kernels recompute P from
  * BF16 Q and K with FP32 softmax statistics, round dO, P and dS to BF16 as
- * matrix operands and accumulate in FP32; FP32 runs FMA kernels throughout.
+ * matrix operands and accumulate in FP32; FP32 is FP32 throughout.
  * Asynchronous on `stream`; the descriptors are copied from a pinned host
  * buffer the library owns.  The workspace query returns 0 for invalid
  * arguments.                                                               */
