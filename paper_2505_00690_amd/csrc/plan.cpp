@@ -124,8 +124,8 @@ bool finish_plan(const PlanModel& m, std::vector<ImgDesc>& imgs, int64_t T, Plan
       // Every batch of the bucket fits: a part's streamed items number at
       // most sum ceil(ntok / 128) <= T / 128 + n, its resident images at
       // most n, each of at most kResMaxTiles key tiles, its images at most
-      // kMaxTokens tokens.  Both attention kernels are launched (their live
-      // counts may be 0).
+      // kMaxTokens tokens.  The resident kernel is launched too where the
+      // option forces it (either's live count may be 0 then).
       q.T_cap = cap_tokens(q.T);
       q.n_cap = cap_images(q.n);
       q.items_cap = (q.T_cap + kAttnQ - 1) / kAttnQ + q.n_cap;
